@@ -11,7 +11,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "liblighthouse.so")
 BUILD = os.path.join(HERE, "_build")
-SOURCES = ["api.cpp", "k_pool_score.hip", "k_select.hip", "k_gather_scatter.hip", "k_sdpa.hip", "k_sdpa_mfma.hip"]
+SOURCES = ["api.cpp", "k_pool_score.hip", "k_select.hip", "k_gather_scatter.hip", "k_sdpa.hip", "k_sdpa_f32.hip",
+           "k_sdpa_mfma.hip"]
 # measurement probe, a library of its own (not part of the attention path)
 CEILING_SOURCE = "k_ceiling.hip"
 CEILING_OUT = os.path.join(HERE, "libceiling.so")

@@ -1,7 +1,6 @@
 // k_sdpa.hip -- dense causal SDPA on the gathered sub-sequence (Sec. 3.5, Eq. attn-sub with
-// Eq. sdpa): dispatch, the Delta = rowsum(dO * O) kernel of the backward, and the fp32 path
-// (plain per-row kernels, a thread per row, used for fp32 problems). The bf16 MFMA kernels are
-// in k_sdpa_mfma.hip.
+// Eq. sdpa): dispatch and the Delta = rowsum(dO * O) kernel of the backward. The bf16 kernels are
+// in k_sdpa_mfma.hip, the fp32 kernels in k_sdpa_f32.hip.
 #include <mutex>
 
 #include "lh_common.h"
@@ -11,6 +10,11 @@ hipError_t lh_launch_sdpa_fwd_bf16(const LhShape& s, const void* qs, const void*
 hipError_t lh_launch_sdpa_bwd_bf16(const LhShape& s, const void* qs, const void* ks, const void* vs,
                                    const void* dos, const float* lse, const float* delta, void* dqs,
                                    void* dks, void* dvs, hipStream_t st);
+hipError_t lh_launch_sdpa_fwd_f32(const LhShape& s, const void* qs, const void* ks, const void* vs, void* os,
+                                  float* lse, hipStream_t st);
+hipError_t lh_launch_sdpa_bwd_f32(const LhShape& s, const void* qs, const void* ks, const void* vs, const void* dos,
+                                  const float* lse, const float* delta, void* dqs, void* dks, void* dvs,
+                                  hipStream_t st);
 hipError_t lh_launch_sdpa_fwd_idx(const LhShape& s, const void* q, const void* k, const void* v, const void* qp,
                                   const void* kp, const void* vp, const int32_t* idx, void* os, float* lse,
                                   hipStream_t st);
@@ -42,163 +46,6 @@ __global__ void __launch_bounds__(256) sdpa_delta(const T* __restrict__ O, const
   if (row < rows && cc == 0) delta[row] = acc;
 }
 
-// ------------------------------------------------------------------ fp32 kernels (a thread per row)
-constexpr int RT = 64;  // rows per workgroup
-constexpr int TT = 32;  // rows per LDS tile
-
-template <int D>
-__global__ void __launch_bounds__(RT) sdpa_fwd_f32(const float* __restrict__ Q, const float* __restrict__ K,
-                                                   const float* __restrict__ V, float* __restrict__ O,
-                                                   float* __restrict__ LSE, int64_t S, float scale, int Hq,
-                                                   int Hs, int Gq) {
-  __shared__ float Ks[TT][D];
-  __shared__ float Vs[TT][D];
-  const int64_t bh = blockIdx.y;
-  const int64_t kvh = (bh / Hq) * Hs + (bh % Hq) / Gq;  // selection head: rows of ks, vs
-  const int64_t nqt = (S + RT - 1) / RT;
-  const int64_t q0 = (nqt - 1 - (int64_t)blockIdx.x) * RT;
-  const int64_t myq = q0 + threadIdx.x;
-  const float* Qh = Q + bh * S * D;
-  float q[D], o[D];
-  for (int c = 0; c < D; ++c) {
-    q[c] = myq < S ? Qh[myq * D + c] : 0.0f;
-    o[c] = 0.0f;
-  }
-  float m = -INFINITY, l = 0.0f;
-  int64_t kend = q0 + RT;
-  if (kend > S) kend = S;
-  for (int64_t k0 = 0; k0 < kend; k0 += TT) {
-    for (int e = threadIdx.x; e < TT * D; e += RT) {
-      const int64_t key = k0 + e / D;
-      Ks[e / D][e % D] = key < S ? K[(kvh * S + key) * D + e % D] : 0.0f;
-      Vs[e / D][e % D] = key < S ? V[(kvh * S + key) * D + e % D] : 0.0f;
-    }
-    __syncthreads();
-    for (int t = 0; t < TT; ++t) {
-      const int64_t key = k0 + t;
-      if (key > myq || key >= S) break;
-      float s = 0.0f;
-      for (int c = 0; c < D; ++c) s += q[c] * Ks[t][c];
-      s *= scale;
-      const float mn = fmaxf(m, s);
-      const float al = expf(m - mn), pv = expf(s - mn);
-      l = l * al + pv;
-      for (int c = 0; c < D; ++c) o[c] = o[c] * al + pv * Vs[t][c];
-      m = mn;
-    }
-    __syncthreads();
-  }
-  if (myq < S) {
-    for (int c = 0; c < D; ++c) O[(bh * S + myq) * D + c] = o[c] / l;
-    LSE[bh * S + myq] = m + logf(l);
-  }
-}
-
-template <int D>
-__global__ void __launch_bounds__(RT) sdpa_bwd_dq_f32(const float* __restrict__ Q, const float* __restrict__ K,
-                                                      const float* __restrict__ V, const float* __restrict__ dO,
-                                                      const float* __restrict__ LSE, const float* __restrict__ DELTA,
-                                                      float* __restrict__ dQ, int64_t S, float scale, int Hq,
-                                                      int Hs, int Gq) {
-  __shared__ float Ks[TT][D];
-  __shared__ float Vs[TT][D];
-  const int64_t bh = blockIdx.y;
-  const int64_t kvh = (bh / Hq) * Hs + (bh % Hq) / Gq;
-  const int64_t nqt = (S + RT - 1) / RT;
-  const int64_t q0 = (nqt - 1 - (int64_t)blockIdx.x) * RT;
-  const int64_t myq = q0 + threadIdx.x;
-  float q[D], go[D], dq[D];
-  for (int c = 0; c < D; ++c) {
-    q[c] = myq < S ? Q[(bh * S + myq) * D + c] : 0.0f;
-    go[c] = myq < S ? dO[(bh * S + myq) * D + c] : 0.0f;
-    dq[c] = 0.0f;
-  }
-  const float lse = myq < S ? LSE[bh * S + myq] : 0.0f;
-  const float dl = myq < S ? DELTA[bh * S + myq] : 0.0f;
-  int64_t kend = q0 + RT;
-  if (kend > S) kend = S;
-  for (int64_t k0 = 0; k0 < kend; k0 += TT) {
-    for (int e = threadIdx.x; e < TT * D; e += RT) {
-      const int64_t key = k0 + e / D;
-      Ks[e / D][e % D] = key < S ? K[(kvh * S + key) * D + e % D] : 0.0f;
-      Vs[e / D][e % D] = key < S ? V[(kvh * S + key) * D + e % D] : 0.0f;
-    }
-    __syncthreads();
-    for (int t = 0; t < TT; ++t) {
-      const int64_t key = k0 + t;
-      if (key > myq || key >= S) break;
-      float s = 0.0f, dp = 0.0f;
-      for (int c = 0; c < D; ++c) {
-        s += q[c] * Ks[t][c];
-        dp += go[c] * Vs[t][c];
-      }
-      const float pv = expf(s * scale - lse);
-      const float ds = pv * (dp - dl);
-      for (int c = 0; c < D; ++c) dq[c] += ds * Ks[t][c];
-    }
-    __syncthreads();
-  }
-  if (myq < S)
-    for (int c = 0; c < D; ++c) dQ[(bh * S + myq) * D + c] = dq[c] * scale;
-}
-
-template <int D>
-__global__ void __launch_bounds__(RT) sdpa_bwd_dkdv_f32(const float* __restrict__ Q, const float* __restrict__ K,
-                                                        const float* __restrict__ V, const float* __restrict__ dO,
-                                                        const float* __restrict__ LSE, const float* __restrict__ DELTA,
-                                                        float* __restrict__ dK, float* __restrict__ dV, int64_t S,
-                                                        float scale, int Hq, int Hs, int Gq) {
-  __shared__ float Qs[TT][D];
-  __shared__ float dOs[TT][D];
-  __shared__ float ls[TT], dls[TT];
-  const int64_t bs = blockIdx.y;  // selection head: its keys gather the gradients of its Gq query heads
-  const int64_t bh = bs;
-  const int64_t k0 = (int64_t)blockIdx.x * RT;
-  const int64_t myk = k0 + threadIdx.x;
-  float kr[D], vr[D], dk[D], dv[D];
-  for (int c = 0; c < D; ++c) {
-    kr[c] = myk < S ? K[(bh * S + myk) * D + c] : 0.0f;
-    vr[c] = myk < S ? V[(bh * S + myk) * D + c] : 0.0f;
-    dk[c] = dv[c] = 0.0f;
-  }
-  for (int mq = 0; mq < Gq; ++mq)
-  for (int64_t qt = k0; qt < S; qt += TT) {
-    const int64_t bq = (bs / Hs) * Hq + (bs % Hs) * Gq + mq;  // member query head
-    for (int e = threadIdx.x; e < TT * D; e += RT) {
-      const int64_t q = qt + e / D;
-      Qs[e / D][e % D] = q < S ? Q[(bq * S + q) * D + e % D] : 0.0f;
-      dOs[e / D][e % D] = q < S ? dO[(bq * S + q) * D + e % D] : 0.0f;
-    }
-    for (int e = threadIdx.x; e < TT; e += RT) {
-      ls[e] = qt + e < S ? LSE[bq * S + qt + e] : 0.0f;
-      dls[e] = qt + e < S ? DELTA[bq * S + qt + e] : 0.0f;
-    }
-    __syncthreads();
-    for (int t = 0; t < TT; ++t) {
-      const int64_t q = qt + t;
-      if (q >= S) break;
-      if (q < myk) continue;
-      float s = 0.0f, dp = 0.0f;
-      for (int c = 0; c < D; ++c) {
-        s += Qs[t][c] * kr[c];
-        dp += dOs[t][c] * vr[c];
-      }
-      const float pv = expf(s * scale - ls[t]);
-      const float ds = pv * (dp - dls[t]);
-      for (int c = 0; c < D; ++c) {
-        dk[c] += ds * Qs[t][c];
-        dv[c] += pv * dOs[t][c];
-      }
-    }
-    __syncthreads();
-  }
-  if (myk < S)
-    for (int c = 0; c < D; ++c) {
-      dK[(bh * S + myk) * D + c] = dk[c] * scale;
-      dV[(bh * S + myk) * D + c] = dv[c];
-    }
-}
-
 }  // namespace lh
 
 using namespace lh;
@@ -207,16 +54,7 @@ hipError_t lh_launch_sdpa_fwd(const LhShape& s, const void* qs, const void* ks, 
                               void* os, float* lse, hipStream_t st) {
   if (s.S == 0) return hipSuccess;
   if (s.dtype == LH_BF16) return lh_launch_sdpa_fwd_bf16(s, qs, ks, vs, os, lse, st);
-  const int64_t BH = s.B * s.Hq;
-  dim3 grid((unsigned)((s.S + RT - 1) / RT), (unsigned)BH);
-  auto q = (const float*)qs;
-  auto k = (const float*)ks;
-  auto v = (const float*)vs;
-  if (s.D == 128)
-    hipLaunchKernelGGL(sdpa_fwd_f32<128>, grid, dim3(RT), 0, st, q, k, v, (float*)os, lse, s.S, s.scale, s.Hq, s.Hs, s.Gq);
-  else
-    hipLaunchKernelGGL(sdpa_fwd_f32<64>, grid, dim3(RT), 0, st, q, k, v, (float*)os, lse, s.S, s.scale, s.Hq, s.Hs, s.Gq);
-  return hipGetLastError();
+  return lh_launch_sdpa_fwd_f32(s, qs, ks, vs, os, lse, st);
 }
 
 static hipError_t launch_delta(const LhShape& s, const void* os, const void* dos, float* delta, hipStream_t st) {
@@ -251,31 +89,11 @@ hipError_t lh_launch_sdpa_bwd_indexed(const LhShape& s, const void* q, const voi
 hipError_t lh_launch_sdpa_bwd(const LhShape& s, const void* qs, const void* ks, const void* vs,
                               const void* os, const float* lse, const void* dos, void* dqs,
                               void* dks, void* dvs, float* delta, hipStream_t st) {
-  const int64_t BH = s.B * s.Hq;
   if (s.S == 0) return hipSuccess;
-  {
-    hipError_t e = launch_delta(s, os, dos, delta, st);
-    if (e != hipSuccess) return e;
-  }
+  const hipError_t e = launch_delta(s, os, dos, delta, st);
+  if (e != hipSuccess) return e;
   if (s.dtype == LH_BF16) return lh_launch_sdpa_bwd_bf16(s, qs, ks, vs, dos, lse, delta, dqs, dks, dvs, st);
-  auto q = (const float*)qs;
-  auto k = (const float*)ks;
-  auto v = (const float*)vs;
-  auto g = (const float*)dos;
-  dim3 gq((unsigned)((s.S + RT - 1) / RT), (unsigned)BH);
-  dim3 gk((unsigned)((s.S + RT - 1) / RT), (unsigned)(s.B * s.Hs));  // per selection head
-  if (s.D == 128) {
-    hipLaunchKernelGGL(sdpa_bwd_dkdv_f32<128>, gk, dim3(RT), 0, st, q, k, v, g, lse, delta, (float*)dks, (float*)dvs,
-                       s.S, s.scale, s.Hq, s.Hs, s.Gq);
-    hipLaunchKernelGGL(sdpa_bwd_dq_f32<128>, gq, dim3(RT), 0, st, q, k, v, g, lse, delta, (float*)dqs, s.S, s.scale,
-                       s.Hq, s.Hs, s.Gq);
-  } else {
-    hipLaunchKernelGGL(sdpa_bwd_dkdv_f32<64>, gk, dim3(RT), 0, st, q, k, v, g, lse, delta, (float*)dks, (float*)dvs,
-                       s.S, s.scale, s.Hq, s.Hs, s.Gq);
-    hipLaunchKernelGGL(sdpa_bwd_dq_f32<64>, gq, dim3(RT), 0, st, q, k, v, g, lse, delta, (float*)dqs, s.S, s.scale,
-                       s.Hq, s.Hs, s.Gq);
-  }
-  return hipGetLastError();
+  return lh_launch_sdpa_bwd_f32(s, qs, ks, vs, dos, lse, delta, dqs, dks, dvs, st);
 }
 
 // ------------------------------------------------------------------ scratch of lh_sdpa_bwd_noalloc

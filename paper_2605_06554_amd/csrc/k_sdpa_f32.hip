@@ -1,0 +1,512 @@
+// k_sdpa_f32.hip -- fp32 causal SDPA on the gathered sub-sequence with fp32 MFMA
+// (Sec. 3.5, Eq. attn-sub with Eq. sdpa): forward, and the deterministic backward (dK/dV and dQ
+// workgroups in one launch), per (b, hq) over [S, D] rows.
+//
+// Bound and split. v_mfma_f32_32x32x2_f32 takes 64 clocks for 4096 operations, so a 32 x 32 tile
+// of one product at D = 128 is 4096 clocks of one SIMD, against a few hundred for its softmax
+// and about 2000 for the latency of its loads: the kernels are bound by the matrix unit as soon
+// as every SIMD has a wave. fp32 problems are small (a few thousand rows, a few heads), so the
+// split is for many waves: a workgroup owns 32 rows, and its NF waves share out the 32-row tiles
+// that those rows meet (wave f takes tiles f, f + NF, ...). Each wave streams its tiles into LDS
+// buffers of its own, without a barrier in the loop: the two operand tiles are used in different
+// phases, so each is reloaded as soon as its last phase is done and lands under the next phase.
+// The waves' partial results are summed in LDS at the end, in wave order (deterministic).
+// Measured against a thread per row (64-row workgroups, fp32 FMAs from LDS, registers spilled):
+// a layer's forward and backward at S = 2257, 8 query heads, D = 128 took 71.7 ms and takes
+// 0.64 ms; at S = 832, 2 heads, D = 64, 2.85 ms and 0.15 ms. The error against 64 bits fell too
+// (1.2e-6 to 7e-7, 7e-7 to 4e-7 of the 2-norm, dK at worst).
+//
+// Layout facts (lane l of a wave, h = l / 32):
+//   MFMA 32x32x2: A[m = l % 32][k = h], B[k = h][n = l % 32],
+//                 C[m = 8 (i / 4) + 4 h + i % 4][n = l % 32], i = 0..15.
+//   A product over D takes its k in the order 8 kk + 4 h + j, so a lane's operands of four MFMAs
+//   are one 16-byte read. A product over the 32 rows of a tile takes row 8 (i / 4) + 4 h + i % 4
+//   at step i, so accumulator element i is that step's operand as it is.
+//
+// LDS tiles: 32 rows of D floats, chunk c (16 bytes) of row r at position c ^ (r mod chunks), so
+// that the lanes reading one chunk of consecutive rows hit different banks.
+#include <float.h>
+
+#include "lh_common.h"
+
+namespace lh {
+
+constexpr float kLog2eF = 1.4426950408889634f;
+
+__device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+
+// Waits until at most N of this wave's vector-memory loads are outstanding and its LDS reads
+// have completed. The empty asm statements keep the compiler from moving accesses across.
+template <int N>
+__device__ __forceinline__ void wait_loads() {
+  static_assert(N >= 0 && N < 64, "vmcnt holds 6 bits");
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));
+  asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ void wait_lds_reads() {  // vmcnt 63: loads in flight may stay
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4));
+  asm volatile("" ::: "memory");
+}
+
+// One wave's view of 32-row tiles of D floats.
+template <int D>
+struct Tile32 {
+  static constexpr int CPR = D / 4;            // 16-byte chunks per row
+  static constexpr int RB = 4 * D;             // bytes per row
+  static constexpr int NL = 32 * CPR / 64;     // 1 KB load instructions per tile
+  int row0;    // row operand: byte offset of chunk h of row l % 32
+  int col[4];  // column operand: offsets for rows 4 h + b (b = 0..3), column l % 32
+  __device__ __forceinline__ explicit Tile32(int lane) {
+    const int h = lane >> 5, r = lane & 31;
+    row0 = r * RB + ((h ^ (r & (CPR - 1))) << 4);
+#pragma unroll
+    for (int b = 0; b < 4; ++b) col[b] = (4 * h + b) * RB + (((r >> 2) ^ (4 * h + b)) << 4) + 4 * (r & 3);
+  }
+  // floats 8 kk + 4 h .. + 3 of row l % 32
+  __device__ __forceinline__ float4 row(const float* t, int kk) const {
+    return *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(t) + (row0 ^ (kk << 5)));
+  }
+  // element [8 (i / 4) + 4 h + i % 4][32 db + l % 32]
+  __device__ __forceinline__ float at(const float* t, int i, int db) const {
+    const int a = i >> 2, b = i & 3;
+    return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(t) + col[b] + 8 * a * RB +
+                                           128 * (db ^ (a & (CPR / 8 - 1))));
+  }
+  // rows r0 .. r0 + 31 of src [S, D] (rows past S read row S - 1) into the tile, straight to LDS
+  static __device__ __forceinline__ void load(float* t, const float* src, int r0, int S, int lane) {
+    const char* base = reinterpret_cast<const char*>(src + (int64_t)r0 * D);
+    const int lim = S - 1 - r0;
+#pragma unroll
+    for (int j = 0; j < NL; ++j) {
+      const int pos = j * 64 + lane, r = pos / CPR, c = (pos % CPR) ^ (r & (CPR - 1));
+      const int rr = r < lim ? r : lim;
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(base + rr * RB + c * 16),
+                                       (__attribute__((address_space(3))) void*)(t + j * 256), 16, 0, 0);
+    }
+  }
+};
+
+// Row l % 32 of 32 rows from r0 in registers: element 4 kk + j is column 8 kk + 4 h + j.
+template <int D>
+__device__ __forceinline__ void load_row_regs(const float* src, int row, int h, float* out) {
+#pragma unroll
+  for (int kk = 0; kk < D / 8; ++kk) {
+    const float4 x = *reinterpret_cast<const float4*>(src + (int64_t)row * D + 8 * kk + 4 * h);
+    out[4 * kk] = x.x, out[4 * kk + 1] = x.y, out[4 * kk + 2] = x.z, out[4 * kk + 3] = x.w;
+  }
+}
+
+// acc += tile (rows = m) x regs^T (rows = n) over D. Two operand reads (8 MFMAs, 512 clocks) run
+// ahead of the MFMAs that use them: alone on its SIMD, a wave otherwise waits out each read.
+template <int D>
+__device__ __forceinline__ f32x16 rows_product(const Tile32<D>& tl, const float* t, const float* regs, f32x16 acc) {
+  float4 cur[2] = {tl.row(t, 0), tl.row(t, 1)};
+#pragma unroll
+  for (int kk = 0; kk < D / 8; kk += 2) {
+    float4 nxt[2] = {cur[0], cur[1]};
+    if (kk + 2 < D / 8) nxt[0] = tl.row(t, kk + 2), nxt[1] = tl.row(t, kk + 3);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      acc = mfma_f32(cur[u].x, regs[4 * (kk + u)], acc);
+      acc = mfma_f32(cur[u].y, regs[4 * (kk + u) + 1], acc);
+      acc = mfma_f32(cur[u].z, regs[4 * (kk + u) + 2], acc);
+      acc = mfma_f32(cur[u].w, regs[4 * (kk + u) + 3], acc);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    cur[0] = nxt[0], cur[1] = nxt[1];
+  }
+  return acc;
+}
+
+// acc[d] += product over the tile's 32 rows of its columns and x (element i: row 8 (i / 4) + 4 h +
+// i % 4). XA: x is the row operand (rows of the result come from x), else the column operand. The
+// reads of the next four rows run ahead of the MFMAs.
+template <int D, bool XA>
+__device__ __forceinline__ void cols_product(const Tile32<D>& tl, const float* t, f32x16 x, f32x16* acc) {
+  constexpr int ND = D / 32, G = 128 / D;  // G steps of ND columns: 4 reads in flight
+  float cur[G][ND];
+#pragma unroll
+  for (int g = 0; g < G; ++g)
+#pragma unroll
+    for (int d = 0; d < ND; ++d) cur[g][d] = tl.at(t, g, d);
+#pragma unroll
+  for (int i = 0; i < 16; i += G) {
+    float nxt[G][ND];
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int d = 0; d < ND; ++d) nxt[g][d] = i + G < 16 ? tl.at(t, i + G + g, d) : 0.0f;
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int d = 0; d < ND; ++d)
+        acc[d] = XA ? mfma_f32(x[i + g], cur[g][d], acc[d]) : mfma_f32(cur[g][d], x[i + g], acc[d]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int d = 0; d < ND; ++d) cur[g][d] = nxt[g][d];
+  }
+}
+
+// A wave's accumulators to LDS: unit u = 4 d + g holds elements 4 g .. 4 g + 3 of acc[d].
+template <int D>
+__device__ __forceinline__ void put_acc(float* dst, const f32x16* acc, int lane) {
+#pragma unroll
+  for (int d = 0; d < D / 32; ++d)
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      *reinterpret_cast<float4*>(dst + ((4 * d + g) * 64 + lane) * 4) =
+          make_float4(acc[d][4 * g], acc[d][4 * g + 1], acc[d][4 * g + 2], acc[d][4 * g + 3]);
+}
+__device__ __forceinline__ float4 get_unit(const float* src, int u, int lane) {
+  return *reinterpret_cast<const float4*>(src + (u * 64 + lane) * 4);
+}
+
+// Workgroups in linear-id order take the longest blocks of every head first, and with a head
+// count that is a multiple of 8 every block of a head lands on one XCD.
+struct F32Pos {
+  int rank;
+  int64_t head;
+};
+__device__ __forceinline__ F32Pos f32_pos(int64_t lin, int64_t heads) { return F32Pos{(int)(lin / heads), lin % heads}; }
+
+// ------------------------------------------------------------------ forward
+template <int D, int NF>
+__global__ void __launch_bounds__(64 * NF, D == 64 ? 2 : 1)
+sdpa_fwd_f32(const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
+             float* __restrict__ O, float* __restrict__ LSE, int S, float scale, int Hq, int Hs, int Gq) {
+  using T = Tile32<D>;
+  __shared__ __align__(16) float Kt[NF][32 * D], Vt[NF][32 * D];
+  __shared__ float ms[NF][32], ls[NF][32];
+  const int lane = threadIdx.x & 63, f = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int h = lane >> 5, r32 = lane & 31;
+  const int nblk = (S + 31) / 32;
+  const int64_t heads = (int64_t)gridDim.x / nblk;
+  const F32Pos pos = f32_pos(blockIdx.x, heads);
+  const int64_t bh = pos.head;
+  const int qb = nblk - 1 - pos.rank, q0 = 32 * qb, myq = q0 + r32;
+  const int64_t kvh = (bh / Hq) * Hs + (bh % Hq) / Gq;  // selection head: rows of ks, vs
+  const float* Kh = K + kvh * S * D;
+  const float* Vh = V + kvh * S * D;
+  const float sl2 = scale * kLog2eF;
+  float* kt = Kt[f];
+  float* vt = Vt[f];
+  const T tl(lane);
+  float q[D / 2];
+  load_row_regs<D>(Q + bh * S * D, myq < S ? myq : S - 1, h, q);
+  f32x16 o[D / 32];
+#pragma unroll
+  for (int d = 0; d < D / 32; ++d) o[d] = f32x16{};
+  // the running maximum of the unscaled logits starts at the lowest finite value: a masked logit
+  // (-inf) of a row without any key yet then has weight exp2(-inf) = 0
+  float m = -FLT_MAX, l = 0.0f;
+  const int nt = qb + 1;  // key tiles 0 .. qb; only the last is masked
+  if (f < nt) {
+    T::load(kt, Kh, 32 * f, S, lane);
+    T::load(vt, Vh, 32 * f, S, lane);
+  }
+  for (int t = f; t < nt; t += NF) {
+    const int tn = t + NF < nt ? t + NF : t;  // the last tile is loaded once more, unused
+    wait_loads<T::NL>();  // the K tile has landed
+    f32x16 s = rows_product<D>(tl, kt, q, f32x16{});
+    wait_lds_reads();
+    T::load(kt, Kh, 32 * tn, S, lane);
+    if (t == nt - 1) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (32 * t + 8 * (i >> 2) + 4 * h + (i & 3) > myq) s[i] = -INFINITY;
+    }
+    float mx = s[0];
+#pragma unroll
+    for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    if (__builtin_amdgcn_ballot_w64(mx > m) != 0) {
+      const float mn = fmaxf(m, mx), al = __builtin_amdgcn_exp2f((m - mn) * sl2);
+      l *= al;
+#pragma unroll
+      for (int d = 0; d < D / 32; ++d)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[d][i] *= al;
+      m = mn;
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s[i] = __builtin_amdgcn_exp2f((s[i] - m) * sl2);
+    float sum = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sum += s[i];
+    l += sum;
+    wait_loads<T::NL>();  // the V tile has landed
+    cols_product<D, false>(tl, vt, s, o);
+    wait_lds_reads();
+    T::load(vt, Vh, 32 * tn, S, lane);
+  }
+  l += __shfl_xor(l, 32, 64);
+  wait_loads<0>();
+  put_acc<D>(kt, o, lane);
+  if (h == 0) ms[f][r32] = m, ls[f][r32] = l;
+  __syncthreads();
+  float M = ms[0][r32], lt = 0.0f, w[NF];
+#pragma unroll
+  for (int x = 1; x < NF; ++x) M = fmaxf(M, ms[x][r32]);
+#pragma unroll
+  for (int x = 0; x < NF; ++x) {
+    w[x] = __builtin_amdgcn_exp2f((ms[x][r32] - M) * sl2);  // 0 for a wave without a key of the row
+    lt += w[x] * ls[x][r32];
+  }
+  if (myq >= S) return;
+  constexpr int NU = D / 8 / NF;  // units of the output per wave
+  const float inv = 1.0f / lt;
+#pragma unroll
+  for (int y = 0; y < NU; ++y) {
+    const int u = f * NU + y;
+    float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+    for (int x = 0; x < NF; ++x) {
+      const float4 b = get_unit(Kt[x], u, lane);
+      a.x += w[x] * b.x, a.y += w[x] * b.y, a.z += w[x] * b.z, a.w += w[x] * b.w;
+    }
+    *reinterpret_cast<float4*>(O + (bh * S + myq) * D + 8 * u + 4 * h) =
+        make_float4(a.x * inv, a.y * inv, a.z * inv, a.w * inv);
+  }
+  if (f == 0 && h == 0) LSE[bh * S + myq] = M * scale + logf(lt);
+}
+
+// ------------------------------------------------------------------ backward
+struct BwdF32 {
+  const float *q, *k, *v, *go, *lse, *delta;
+  float *dq, *dk, *dv;
+  int64_t kblocks;  // dK/dV workgroups (the first of the launch); the rest are dQ workgroups
+  int64_t kheads, qheads;
+  int S, Hq, Hs, Gq;
+  float scale;
+};
+
+// dQ of 32 query rows: dP^T = V dO^T (the chain starts from -Delta), S^T = K Q^T,
+// dQ^T += K^T dS^T.
+template <int D, int NF>
+__device__ __forceinline__ void dq_block(const BwdF32& a, int64_t lin, float (*At)[32 * D], float (*Bt)[32 * D],
+                                         int lane, int f) {
+  using T = Tile32<D>;
+  const int h = lane >> 5, r32 = lane & 31, S = a.S;
+  const int nblk = (S + 31) / 32;
+  const F32Pos pos = f32_pos(lin, a.qheads);
+  const int64_t bh = pos.head;
+  const int qb = nblk - 1 - pos.rank, myq = 32 * qb + r32;
+  const int64_t kvh = (bh / a.Hq) * a.Hs + (bh % a.Hq) / a.Gq;
+  const float* Kh = a.k + kvh * S * D;
+  const float* Vh = a.v + kvh * S * D;
+  float* kt = At[f];
+  float* vt = Bt[f];
+  const T tl(lane);
+  const int row = myq < S ? myq : S - 1;
+  float q[D / 2], go[D / 2];
+  load_row_regs<D>(a.q + bh * S * D, row, h, q);
+  load_row_regs<D>(a.go + bh * S * D, row, h, go);
+  const float lse = a.lse[bh * S + row], ndl = -a.delta[bh * S + row];
+  f32x16 dq[D / 32];
+#pragma unroll
+  for (int d = 0; d < D / 32; ++d) dq[d] = f32x16{};
+  const int nt = qb + 1;
+  if (f < nt) {
+    T::load(vt, Vh, 32 * f, S, lane);
+    T::load(kt, Kh, 32 * f, S, lane);
+  }
+  for (int t = f; t < nt; t += NF) {
+    const int tn = t + NF < nt ? t + NF : t;
+    wait_loads<T::NL>();  // V
+    f32x16 dp;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) dp[i] = ndl;
+    dp = rows_product<D>(tl, vt, go, dp);
+    wait_lds_reads();
+    T::load(vt, Vh, 32 * tn, S, lane);
+    wait_loads<T::NL>();  // K
+    f32x16 s = rows_product<D>(tl, kt, q, f32x16{});
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], a.scale, -lse) * kLog2eF);
+      if (t == nt - 1 && 32 * t + 8 * (i >> 2) + 4 * h + (i & 3) > myq) p = 0.0f;
+      s[i] = p * dp[i];
+    }
+    cols_product<D, false>(tl, kt, s, dq);
+    wait_lds_reads();
+    T::load(kt, Kh, 32 * tn, S, lane);
+  }
+  wait_loads<0>();
+  put_acc<D>(kt, dq, lane);
+  __syncthreads();
+  if (myq >= S) return;
+  constexpr int NU = D / 8 / NF;
+#pragma unroll
+  for (int y = 0; y < NU; ++y) {
+    const int u = f * NU + y;
+    float4 x = get_unit(At[0], u, lane);
+#pragma unroll
+    for (int w = 1; w < NF; ++w) {
+      const float4 b = get_unit(At[w], u, lane);
+      x.x += b.x, x.y += b.y, x.z += b.z, x.w += b.w;
+    }
+    *reinterpret_cast<float4*>(a.dq + (bh * S + myq) * D + 8 * u + 4 * h) =
+        make_float4(x.x * a.scale, x.y * a.scale, x.z * a.scale, x.w * a.scale);
+  }
+}
+
+// dK, dV of 32 keys of a selection head, summed over its Gq query heads: dP = dO V^T (from
+// -Delta), S = Q K^T, dV += P^T dO, dK += dS^T Q. A wave's tiles run over (head, query tile).
+template <int D, int NF>
+__device__ __forceinline__ void dkdv_block(const BwdF32& a, int64_t lin, float (*At)[32 * D], float (*Bt)[32 * D],
+                                           float (*st)[64], int lane, int f) {
+  using T = Tile32<D>;
+  const int h = lane >> 5, r32 = lane & 31, S = a.S;
+  const F32Pos pos = f32_pos(lin, a.kheads);
+  const int64_t bs = pos.head;
+  const int kb = pos.rank, mykey = 32 * kb + r32;  // early keys meet the most queries: first
+  const int64_t bh0 = (bs / a.Hs) * a.Hq + (bs % a.Hs) * a.Gq;
+  float* qt = At[f];
+  float* gt = Bt[f];
+  float* stat = st[f];  // lse of the tile's rows, then -Delta
+  const T tl(lane);
+  const int row = mykey < S ? mykey : S - 1;
+  float k[D / 2], v[D / 2];
+  load_row_regs<D>(a.k + bs * S * D, row, h, k);
+  load_row_regs<D>(a.v + bs * S * D, row, h, v);
+  f32x16 dk[D / 32], dv[D / 32];
+#pragma unroll
+  for (int d = 0; d < D / 32; ++d) dk[d] = dv[d] = f32x16{};
+  const int ntq = (S + 31) / 32 - kb;  // query tiles kb .. of one head; only the first is masked
+  const int nt = ntq * a.Gq;
+  float sx = 0.0f;  // lane l < 32: lse of row l of the next tile; l >= 32: Delta of row l - 32
+  auto head_of = [&](int t) __attribute__((always_inline)) { return bh0 + t / ntq; };
+  auto row_of = [&](int t) __attribute__((always_inline)) { return 32 * (kb + t % ntq); };
+  auto load_go = [&](int t) __attribute__((always_inline)) {
+    const int64_t b = head_of(t);
+    const int r0 = row_of(t);
+    T::load(gt, a.go + b * S * D, r0, S, lane);
+    const int r = r0 + r32;
+    sx = (h ? a.delta : a.lse)[b * S + (r < S ? r : S - 1)];
+  };
+  auto load_q = [&](int t) __attribute__((always_inline)) {
+    T::load(qt, a.q + head_of(t) * S * D, row_of(t), S, lane);
+  };
+  if (f < nt) {
+    load_go(f);
+    load_q(f);
+  }
+  for (int t = f; t < nt; t += NF) {
+    const int tn = t + NF < nt ? t + NF : t;
+    wait_loads<T::NL>();  // dO (and lse, Delta)
+    const bool in = row_of(t) + r32 < S;  // rows past S: P = 0
+    stat[lane] = h ? (in ? -sx : 0.0f) : (in ? sx : INFINITY);
+    f32x16 dp;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const float4 d4 = *reinterpret_cast<const float4*>(stat + 32 + 8 * g + 4 * h);
+      dp[4 * g] = d4.x, dp[4 * g + 1] = d4.y, dp[4 * g + 2] = d4.z, dp[4 * g + 3] = d4.w;
+    }
+    dp = rows_product<D>(tl, gt, v, dp);
+    wait_loads<0>();  // Q
+    f32x16 s = rows_product<D>(tl, qt, k, f32x16{});
+    const bool diag = t % ntq == 0;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const float4 l4 = *reinterpret_cast<const float4*>(stat + 8 * g + 4 * h);
+      const float lv[4] = {l4.x, l4.y, l4.z, l4.w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int i = 4 * g + j;
+        float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], a.scale, -lv[j]) * kLog2eF);
+        if (diag && 8 * g + 4 * h + j < r32) p = 0.0f;
+        s[i] = p;
+        dp[i] *= p;
+      }
+    }
+    cols_product<D, true>(tl, gt, s, dv);
+    wait_lds_reads();
+    load_go(tn);
+    cols_product<D, true>(tl, qt, dp, dk);
+    wait_lds_reads();
+    load_q(tn);
+  }
+  wait_loads<0>();
+  put_acc<D>(qt, dk, lane);
+  put_acc<D>(gt, dv, lane);
+  __syncthreads();
+  constexpr int NU = D / 8 / NF;
+#pragma unroll
+  for (int y = 0; y < NU; ++y) {
+    const int u = f * NU + y;
+    float4 x = get_unit(At[0], u, lane), z = get_unit(Bt[0], u, lane);
+#pragma unroll
+    for (int w = 1; w < NF; ++w) {
+      const float4 b = get_unit(At[w], u, lane), c = get_unit(Bt[w], u, lane);
+      x.x += b.x, x.y += b.y, x.z += b.z, x.w += b.w;
+      z.x += c.x, z.y += c.y, z.z += c.z, z.w += c.w;
+    }
+    const float xs[4] = {x.x, x.y, x.z, x.w}, zs[4] = {z.x, z.y, z.z, z.w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {  // C layout: key row 8 g + 4 h + j, column 32 d + l % 32
+      const int key = 32 * kb + 8 * (u & 3) + 4 * h + j;
+      if (key < S) {
+        a.dk[(bs * S + key) * D + 32 * (u >> 2) + r32] = xs[j] * a.scale;
+        a.dv[(bs * S + key) * D + 32 * (u >> 2) + r32] = zs[j];
+      }
+    }
+  }
+}
+
+template <int D, int NF>
+__global__ void __launch_bounds__(64 * NF, D == 64 ? 2 : 1) sdpa_bwd_f32(BwdF32 a) {
+  __shared__ __align__(16) float At[NF][32 * D], Bt[NF][32 * D];
+  __shared__ __align__(16) float st[NF][64];
+  const int lane = threadIdx.x & 63, f = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t lin = blockIdx.x;
+  if (lin < a.kblocks) dkdv_block<D, NF>(a, lin, At, Bt, st, lane, f);
+  else dq_block<D, NF>(a, lin - a.kblocks, At, Bt, lane, f);
+}
+
+}  // namespace lh
+
+using namespace lh;
+
+// Waves per workgroup: 4 at D = 128 (128 KB of tiles); at D = 64, 8 (the same 128 KB) while the
+// row blocks alone do not fill the chip, else 4 (64 KB, two workgroups per CU).
+static bool few_blocks(int64_t blocks) { return blocks <= 256; }
+
+hipError_t lh_launch_sdpa_fwd_f32(const LhShape& s, const void* qs, const void* ks, const void* vs, void* os,
+                                  float* lse, hipStream_t st) {
+  const int64_t blocks = (s.S + 31) / 32 * s.B * s.Hq;
+  const dim3 grid((unsigned)blocks);
+  auto q = (const float*)qs, k = (const float*)ks, v = (const float*)vs;
+  if (s.D == 128)
+    hipLaunchKernelGGL((sdpa_fwd_f32<128, 4>), grid, dim3(256), 0, st, q, k, v, (float*)os, lse, (int)s.S, s.scale,
+                       s.Hq, s.Hs, s.Gq);
+  else if (few_blocks(blocks))
+    hipLaunchKernelGGL((sdpa_fwd_f32<64, 8>), grid, dim3(512), 0, st, q, k, v, (float*)os, lse, (int)s.S, s.scale,
+                       s.Hq, s.Hs, s.Gq);
+  else
+    hipLaunchKernelGGL((sdpa_fwd_f32<64, 4>), grid, dim3(256), 0, st, q, k, v, (float*)os, lse, (int)s.S, s.scale,
+                       s.Hq, s.Hs, s.Gq);
+  return hipGetLastError();
+}
+
+hipError_t lh_launch_sdpa_bwd_f32(const LhShape& s, const void* qs, const void* ks, const void* vs, const void* dos,
+                                  const float* lse, const float* delta, void* dqs, void* dks, void* dvs,
+                                  hipStream_t st) {
+  const int64_t nblk = (s.S + 31) / 32;
+  BwdF32 a{(const float*)qs, (const float*)ks, (const float*)vs, (const float*)dos, lse, delta,
+           (float*)dqs, (float*)dks, (float*)dvs, nblk * s.B * s.Hs, s.B * s.Hs, s.B * s.Hq,
+           (int)s.S, s.Hq, s.Hs, s.Gq, s.scale};
+  const int64_t blocks = nblk * (s.B * s.Hs + s.B * s.Hq);
+  const dim3 grid((unsigned)blocks);
+  if (s.D == 128) hipLaunchKernelGGL((sdpa_bwd_f32<128, 4>), grid, dim3(256), 0, st, a);
+  else if (few_blocks(blocks)) hipLaunchKernelGGL((sdpa_bwd_f32<64, 8>), grid, dim3(512), 0, st, a);
+  else hipLaunchKernelGGL((sdpa_bwd_f32<64, 4>), grid, dim3(256), 0, st, a);
+  return hipGetLastError();
+}

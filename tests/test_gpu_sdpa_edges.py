@@ -1,0 +1,71 @@
+"""SDPA forward and backward at the edges of the kernels' tiles and splits, against the oracle.
+
+L = 1 gives S = N, so every S can be asked for. The sizes sit on both sides of a 32-row block,
+of the blocks that the waves of a workgroup share out, and of the block counts at which another
+split of the rows is launched. With LH_FLAG_GQA_SHARED two query heads share a K, V head, whose
+gradients sum over them."""
+import numpy as np
+import pytest
+import torch
+
+import bf16_floor
+import oracle
+import paper_2605_06554_amd as lh
+from parity import check_close, emulated_floor
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def run_case(S, D, dt, Hq, Hkv, shared, rng, B=1, heads=None):
+    print(f"[sdpa edges] S={S} D={D} {dt} Hq={Hq} Hkv={Hkv} shared={shared}", flush=True)
+    tdt = torch.bfloat16 if dt == "bf16" else torch.float32
+    pr = lh.problem(B, S, Hq, Hkv, D, 2, 1, 0, tdt, flags=lh.LH_FLAG_GQA_SHARED if shared else 0)
+    Hs = lh.selection_heads(pr)
+    x = [torch.from_numpy(rng.standard_normal((B, H, S, D))).to(tdt) for H in (Hq, Hs, Hs, Hq)]
+    qs, ks, vs, dos = (t.to(DEV) for t in x)
+    os_, dqs, dks, dvs = (torch.full_like(t, float("nan")) for t in (qs, qs, ks, vs))
+    lse = torch.empty(B, Hq, S, dtype=torch.float32, device=DEV)
+    lh.lh_sdpa_fwd(pr, qs, ks, vs, os_, lse)
+    lh.lh_sdpa_bwd(pr, qs, ks, vs, os_, lse, dos, dqs, dks, dvs, lh.workspace(pr, lh.LH_OP_SDPA_BWD))
+    torch.cuda.synchronize()
+    sc, G, bf = 1.0 / np.sqrt(D), Hq // Hs, dt == "bf16"
+    for b in range(B):
+        for hs in range(Hs) if heads is None else heads:
+            k, v = x[1][b, hs].double().numpy(), x[2][b, hs].double().numpy()
+            rk, rv = np.zeros((S, D)), np.zeros((S, D))
+            ek, ev = np.zeros((S, D)), np.zeros((S, D))
+            for hq in range(hs * G, hs * G + G):
+                q, do = x[0][b, hq].double().numpy(), x[3][b, hq].double().numpy()
+                ro, rl = oracle.sdpa_fwd(q, k, v, sc)
+                rq, dk, dv = oracle.sdpa_bwd(q, k, v, ro, rl, do, sc)
+                rk += dk
+                rv += dv
+                fo = fq = None
+                if bf:
+                    eo, _ = bf16_floor.sdpa_fwd(q, k, v, sc)
+                    eq, dk, dv = bf16_floor.sdpa_bwd(q, k, v, eo, rl, do, sc)
+                    ek += dk
+                    ev += dv
+                    fo, fq = emulated_floor(eo, ro), emulated_floor(eq, rq)
+                check_close(f"os[{b},{hq}]", os_[b, hq], ro, dt, fo)
+                check_close(f"lse[{b},{hq}]", lse[b, hq], rl, "fp32")
+                check_close(f"dqs[{b},{hq}]", dqs[b, hq], rq, dt, fq)
+            fk = emulated_floor(bf16_floor.round_bf16(ek), rk) if bf else None
+            fv = emulated_floor(bf16_floor.round_bf16(ev), rv) if bf else None
+            check_close(f"dks[{b},{hs}]", dks[b, hs], rk, dt, fk)
+            check_close(f"dvs[{b},{hs}]", dvs[b, hs], rv, dt, fv)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("S", [1, 32, 33, 128, 129, 255, 257])
+def test_fp32_edges(S, D, rng):
+    """A workgroup is 32 rows, its 4 or 8 waves take every 4th or 8th 32-row tile."""
+    run_case(S, D, "fp32", 2, 2, False, rng)
+
+
+@pytest.mark.parametrize("S,D,Hq", [(161, 64, 4), (97, 128, 6), (545, 64, 32)])
+def test_fp32_shared(S, D, Hq, rng):
+    """dK, dV over the query heads of a shared selection; at (545, 64, 32) the row blocks fill the
+    chip and the 4-wave split runs at D = 64."""
+    run_case(S, D, "fp32", Hq, 2, True, rng, heads=[0] if Hq > 8 else None)
