@@ -1,6 +1,6 @@
 // k_sdpa_mfma.hip -- bf16 causal SDPA on the gathered sub-sequence with gfx950 MFMA
 // (Sec. 3.5, Eq. attn-sub with Eq. sdpa): forward, and the deterministic backward
-// (a dK/dV kernel and a dQ kernel), per (b, hq) over [S, D] rows.
+// (dK/dV and dQ workgroups in one launch), per (b, hq) over [S, D] rows.
 //
 // Numerics: v_mfma_f32_32x32x16_bf16 with fp32 accumulation; the softmax runs in the exp2
 // domain with the scale folded into one FMA; P and dS are rounded to bf16 for their products.
@@ -26,54 +26,18 @@
 // different groups. Every lane's LDS offsets are computed once; tile bases are compile-time
 // constants (the tile loop is unrolled over the ring of slots).
 //
-// Occupancy: the forward runs 12 waves per workgroup, 3 per SIMD (at most 168 registers), so
-// that two waves can be in their softmax while a third feeds the MFMA unit. The two backward
-// kernels hold 128 (dK/dV) or 160 (dQ) accumulator and operand registers per lane and run 2
+// Occupancy: with F = 1 (below) the forward runs 12 waves per workgroup, 3 per SIMD (at most 168
+// registers), so that two waves can be in their softmax while a third feeds the MFMA unit. The
+// backward holds 128 (dK/dV) or 160 (dQ) accumulator and operand registers per lane and runs 2
 // waves per SIMD.
 //
-// Pipeline: each kernel keeps an NS-slot ring of tiles in LDS. Before using tile t, a wave
-// waits until at most (NS - 2) tiles' worth of its own LDS-DMA loads are outstanding (vmcnt
-// counts this wave's loads in issue order), then the block barrier publishes tile t from every
-// wave; right after the barrier the loads of tile t + NS - 1 go into the slot tile t - 1 used.
-// Every wave issues the same number of loads per tile (loads past the end read clamped rows
-// into the free slot), so the wait count is a compile-time constant.
+// Pipeline: each kernel keeps a two-slot ring of tiles in LDS. Before using tile t, a wave waits
+// until its own LDS-DMA loads have landed, then the block barrier publishes tile t from every
+// wave; right after the barrier the loads of tile t + 1 go into the slot tile t - 1 used. Loads
+// past the end read clamped rows into the free slot.
 #include <type_traits>
 
 #include "lh_common.h"
-
-#ifndef LH_FW
-#define LH_FW 12  // forward: waves per workgroup (32 query rows each)
-#endif
-#ifndef LH_FEU
-#define LH_FEU 3  // forward: waves per SIMD the register budget targets
-#endif
-#ifndef LH_FK
-#define LH_FK 64  // forward: keys per tile
-#endif
-#ifndef LH_QW
-#define LH_QW 8  // dQ: waves per workgroup (32 query rows each)
-#endif
-#ifndef LH_BK
-#define LH_BK 64  // dQ: keys per tile
-#endif
-#ifndef LH_KWV
-#define LH_KWV 8  // dK/dV: waves per workgroup (32 keys each)
-#endif
-#ifndef LH_KWV_EU
-#define LH_KWV_EU 2  // dK/dV: waves per SIMD the register budget targets
-#endif
-#ifndef LH_CQ
-#define LH_CQ 64  // dK/dV: query rows per tile
-#endif
-#ifndef LH_ORDER
-#define LH_ORDER 1  // 1: blocks ordered by work across all heads (longest first); 0: head by head
-#endif
-#ifndef LH_FNS
-#define LH_FNS 2  // forward: tile slots in the LDS ring
-#endif
-#ifndef LH_QNS
-#define LH_QNS 2  // dQ: tile slots in the LDS ring
-#endif
 
 namespace lh {
 
@@ -90,35 +54,14 @@ constexpr float kRescale = 8.0f;  // lazy rescaling threshold (log2 units)
 template <int N>
 using IC = std::integral_constant<int, N>;
 
-// D = 128 (16 chunks per row): swap the two 2-bit halves of r % 16.
-// D = 64 (8 chunks per row, two rows per 256-byte bank line): a bijection of (r / 2) % 8 whose
-// top bit follows bit 1 of r.
-// Two swizzles of the 16-byte chunks of a row (SW below):
-//   SW = 2: a bijection of r % 16, so the 16 lanes that read one logical chunk of 16 consecutive
-//           rows hit 16 different chunk positions: row and transposed reads are conflict free;
-//   SW = 3: depends on r % 8 only, so rows r and r + 8 share it and a transposed read of rows
-//           r0 + 8 is the read of rows r0 shifted by a constant (one lane offset fewer per
-//           column block), at the price of a 2-way bank conflict on the row reads.
-// D = 64 (8 chunks per row, two rows per 256-byte bank line): a bijection of (r / 2) % 8 whose
-// top bit follows bit 1 of r (SW = 2), or of (r / 2) % 4 (SW = 3).
-#ifndef LH_SWZ_F
-#define LH_SWZ_F 2  // forward
-#endif
-#ifndef LH_SWZ_Q
-#define LH_SWZ_Q 2  // dQ
-#endif
-#ifndef LH_SWZ_K
-#define LH_SWZ_K 2  // dK/dV
-#endif
-template <int D, int SW>
+// Swizzle of the 16-byte chunks of a row. D = 128 (16 chunks per row): swap the two 2-bit halves
+// of r % 16. D = 64 (8 chunks per row, two rows per 256-byte bank line): a bijection of (r / 2) % 8
+// whose top bit follows bit 1 of r. The 16 lanes that read one logical chunk of 16 consecutive
+// rows hit 16 different chunk positions: row and transposed reads are conflict free.
+template <int D>
 __device__ __forceinline__ int swz(int r) {
-  if constexpr (SW == 2) {
-    if constexpr (D == 128) return ((r & 3) << 2) | ((r >> 2) & 3);
-    else return (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
-  } else {
-    if constexpr (D == 128) return ((r & 3) << 2) | ((r >> 2) & 1);
-    else return (((r >> 1) & 1) << 2) | ((r >> 2) & 1);
-  }
+  if constexpr (D == 128) return ((r & 3) << 2) | ((r >> 2) & 3);
+  else return (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
 }
 
 // Byte offsets of one lane inside any swizzled tile (row blocks start at multiples of 16).
@@ -129,19 +72,20 @@ struct LaneOff {
   int trh[D / 32];  // the same 8 rows further (slots 4-7)
 };
 
-template <int D, int SW>
-__device__ __forceinline__ LaneOff<D> lane_offsets(int lane) {
+// rows0: first tile row of this wave's share (a multiple of 32)
+template <int D>
+__device__ __forceinline__ LaneOff<D> lane_offsets(int lane, int rows0) {
   constexpr int RB = 2 * D;
   LaneOff<D> o;
-  const int h = lane >> 5, r = lane & 31;
+  const int h = lane >> 5, r = lane & 31, base = rows0 * RB;
 #pragma unroll
-  for (int kk = 0; kk < D / 16; ++kk) o.row[kk] = r * RB + (((2 * kk + h) ^ swz<D, SW>(r)) << 4);
+  for (int kk = 0; kk < D / 16; ++kk) o.row[kk] = base + r * RB + (((2 * kk + h) ^ swz<D>(r)) << 4);
   const int r0 = 4 * h + ((lane & 15) >> 2);
 #pragma unroll
   for (int d = 0; d < D / 32; ++d) {
     const int chunk = 4 * d + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
-    o.trl[d] = r0 * RB + ((chunk ^ swz<D, SW>(r0)) << 4) + 8 * (lane & 1);
-    o.trh[d] = (r0 + 8) * RB + ((chunk ^ swz<D, SW>(r0 + 8)) << 4) + 8 * (lane & 1);
+    o.trl[d] = base + r0 * RB + ((chunk ^ swz<D>(r0)) << 4) + 8 * (lane & 1);
+    o.trh[d] = base + (r0 + 8) * RB + ((chunk ^ swz<D>(r0 + 8)) << 4) + 8 * (lane & 1);
   }
   return o;
 }
@@ -180,7 +124,7 @@ __device__ __forceinline__ bf16x8 gld8(const bf16_t* p) { return *reinterpret_ca
 template <int D, int TR, int NW>
 __device__ __forceinline__ constexpr int loads_per_wave() { return (TR * D / 512 + NW - 1) / NW; }
 
-template <int D, int TR, int NW, int SW, bool CLAMP>
+template <int D, int TR, int NW, bool CLAMP>
 __device__ __forceinline__ void load_tile_rows(bf16_t* tile, const bf16_t* src, int r0, int S, int w, int lane) {
   constexpr int CPR = D / 8;
   constexpr int BLOCKS = TR * CPR / 64;  // 1 KB blocks of the tile
@@ -192,7 +136,7 @@ __device__ __forceinline__ void load_tile_rows(bf16_t* tile, const bf16_t* src, 
     if (BLOCKS % NW != 0 && blk >= BLOCKS) blk -= BLOCKS;
     const int pos = blk * 64 + lane;
     const int r = pos / CPR;
-    const int c = (pos % CPR) ^ swz<D, SW>(r);
+    const int c = (pos % CPR) ^ swz<D>(r);
     // rows past S read row S - 1; the clamp stays a 32-bit lane offset from the tile's uniform
     // base, so no lane holds a 64-bit address (fewer live registers in every kernel)
     const int rr = CLAMP ? (r < S - 1 - r0 ? r : S - 1 - r0) : r;
@@ -204,10 +148,10 @@ __device__ __forceinline__ void load_tile_rows(bf16_t* tile, const bf16_t* src, 
 
 // r0 and w are uniform: a tile that lies inside the matrix is one scalar base address plus a
 // fixed 32-bit offset per lane; only a tile that crosses row S clamps row by row.
-template <int D, int TR, int NW, int SW>
+template <int D, int TR, int NW>
 __device__ __forceinline__ void load_tile(bf16_t* tile, const bf16_t* src, int r0, int S, int w, int lane) {
-  if (r0 + TR <= S) load_tile_rows<D, TR, NW, SW, false>(tile, src, r0, S, w, lane);
-  else load_tile_rows<D, TR, NW, SW, true>(tile, src, r0, S, w, lane);
+  if (r0 + TR <= S) load_tile_rows<D, TR, NW, false>(tile, src, r0, S, w, lane);
+  else load_tile_rows<D, TR, NW, true>(tile, src, r0, S, w, lane);
 }
 
 // Index-driven rows (the gather fused into the loads). Row m of a gathered head is pyramid id
@@ -227,21 +171,18 @@ struct HeadMap {
   int32_t Hq, Hs, Gq;
 };
 
-// Block order. Blocks are dispatched in linear-id order and go round-robin to the 8 XCDs. With
-// LH_ORDER = 1 linear id = rank * heads + head, where rank 0 is the longest block of a head
-// (most causal tiles): the longest blocks of every head start first, so no long block is left
-// to run alone at the end, and (heads being a multiple of 8) every block of a head lands on the
-// same XCD, whose L2 then holds that head's streamed tiles.
+// Block order. Blocks are dispatched in linear-id order and go round-robin to the 8 XCDs. Linear
+// id = rank * heads + head, where rank 0 is the longest block of a head (most causal tiles): the
+// longest blocks of every head start first, so no long block is left to run alone at the end, and
+// (heads being a multiple of 8) every block of a head lands on the same XCD, whose L2 then holds
+// that head's streamed tiles.
 struct BlockPos {
   int rank;      // 0 = the head's longest block
-  int64_t head;  // blockIdx.y of the head-by-head order
+  int64_t head;
 };
-__device__ __forceinline__ BlockPos block_pos() {
-  if (LH_ORDER) {
-    const int64_t lin = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
-    return BlockPos{(int)(lin / gridDim.y), lin % gridDim.y};
-  }
-  return BlockPos{(int)blockIdx.x, (int64_t)blockIdx.y};
+__device__ __forceinline__ BlockPos block_pos(uint32_t lin, uint32_t heads) {
+  const uint32_t r = lin / heads;
+  return BlockPos{(int)r, (int64_t)(lin - r * heads)};
 }
 
 struct RowSrc {
@@ -285,7 +226,7 @@ __device__ __forceinline__ void tile_ids(const int32_t* idxh, int r0, int S, int
 }
 
 // load_tile with every row read from its pyramid id.
-template <int D, int TR, int NW, int SW>
+template <int D, int TR, int NW>
 __device__ __forceinline__ void load_tile_idx(bf16_t* tile, const RowSrc& src, const int32_t* ids, int w, int lane) {
   constexpr int CPR = D / 8;
   constexpr int BLOCKS = TR * CPR / 64;
@@ -294,7 +235,7 @@ __device__ __forceinline__ void load_tile_idx(bf16_t* tile, const RowSrc& src, c
     int blk = j * NW + w;
     if (BLOCKS % NW != 0 && blk >= BLOCKS) blk -= BLOCKS;
     const int pos = blk * 64 + lane;
-    const int c = (pos % CPR) ^ swz<D, SW>(pos / CPR);
+    const int c = (pos % CPR) ^ swz<D>(pos / CPR);
     const bf16_t* g = rs_row(src, ids[j]) + c * 8;
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
                                      (__attribute__((address_space(3))) void*)(tile + blk * 512), 16, 0, 0);
@@ -312,29 +253,6 @@ __device__ __forceinline__ void sync_tiles() {
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 }
-
-// Ring slots are separate __shared__ arrays (not one indexed array), so the compiler can tell
-// that a load streaming into one slot does not alias reads of another and does not wait for it.
-#define LH_RING(T, name, n)                                                   \
-  __shared__ __align__(16) T name##0[n], name##1[n], name##2[n], name##3[n]; \
-  T* const name[4] = {name##0, name##1, name##2, name##3}
-
-// Calls f(IC<slot>{}, t) for t = t0 .. min(t0 + NS, n) - 1 with slot = t - t0 (compile-time).
-template <int I, int NS>
-struct SlotLoop {
-  template <typename F>
-  static __device__ __forceinline__ void run(int t0, int n, F& f) {
-    if (t0 + I < n) {
-      f(IC<I>{}, t0 + I);
-      SlotLoop<I + 1, NS>::run(t0, n, f);
-    }
-  }
-};
-template <int NS>
-struct SlotLoop<NS, NS> {
-  template <typename F>
-  static __device__ __forceinline__ void run(int, int, F&) {}
-};
 
 // Calls f(IC<t % 2>{}, t) for t = begin .. end - 1: a loop over a two-slot ring that may start
 // on either slot.
@@ -366,33 +284,122 @@ __device__ __forceinline__ void store_qrow(bf16_t* row, const f32x16* acc, float
     }
 }
 
-// ------------------------------------------------------------------ forward
-constexpr int FW = LH_FW, FQ = 32 * LH_FW, FK = LH_FK, FNS = LH_FNS;
+// Ring slots are separate __shared__ arrays (not one indexed array), so the compiler can tell
+// that a load streaming into one slot does not alias reads of another and does not wait for it.
+template <int N>
+struct Ring {  // two slots of two operands
+  bf16_t *a0, *a1, *b0, *b1;
+  template <int SL>
+  __device__ __forceinline__ bf16_t* a() const { return SL ? a1 : a0; }
+  template <int SL>
+  __device__ __forceinline__ bf16_t* b() const { return SL ? b1 : b0; }
+};
 
+// Split of a workgroup's rows and tiles. The R = NW / F row blocks (32 rows each) of a workgroup
+// are each shared by F waves: wave w works on row block w % R and, of every streamed tile of
+// F 32 NB rows, on the NB 32-row blocks from f NB, f = w / R. With F > 1 the F partial
+// accumulators of a row block are summed through LDS at the end, in the order of f.
+//
+// F = 1 has the fewest loads per product (a tile serves every wave) and is what a full chip
+// wants. A problem with few row blocks leaves CUs idle, and its time is that of its longest
+// block, a chain of tiles; F = 2 and 4 make the blocks 2 to 6 times as many and their chains 2
+// to 4 times as short, for as many more tile loads. The rules beside the launches choose.
+template <int F>
+struct FwdCfg {
+  static constexpr int NW = F == 1 ? 12 : 8;  // waves
+  static constexpr int EU = F == 1 ? 3 : 2;   // waves per SIMD the register budget targets
+  static constexpr int NB = F == 1 ? 2 : 1;   // 32-key blocks of a tile per wave
+  static constexpr int R = NW / F, ROWS = 32 * R, TILE = 32 * NB * F;
+};
+template <int F>
+struct BwdCfg {
+  static constexpr int NW = 8, EU = 2;
+  static constexpr int NB = F == 1 ? 2 : 1;
+  static constexpr int R = NW / F, ROWS = 32 * R, TILE = 32 * NB * F;
+};
+
+// Where the backward forms a wave's row block and share at run time. With F = 1 they are w and 0;
+// formed all the same, they steer the compiler to 0.4% less time (71.4 to 71.2 ms at S = 54,272,
+// 32 heads), but in the index-driven kernels, at D = 128, to 60 spilled registers instead of 7.
+template <bool IDX, int F>
+constexpr bool kSplitAt = F > 1 || !IDX;
+
+// Sums the accumulators of the F waves of each row block and hands the sums out: the tile ring
+// (no longer in use) holds the partial accumulators of D / 32 * F / 4 column blocks of every wave
+// at a time. A unit is 4 accumulator elements: out(d, g, x) receives elements 4 g .. 4 g + 3 of
+// column block d, each unit in one of the F waves. wt[x]: weight of wave x's partial.
+template <int D, int F, int R, typename Out>
+__device__ __forceinline__ void combine(const Ring<0>& ring, const f32x16* acc, const float* wt, int w, int lane,
+                                        Out&& out) {
+  constexpr int ND = D / 32 * F / 4;  // column blocks per round: a wave's share is half a slot
+  constexpr int NU = 4 * ND / F;      // units per wave and round
+  static_assert(ND >= 1 && NU >= 1 && F * R == 8, "two waves per slot array");
+  constexpr int HALF = 32 * F * D / 2;  // elements of half a slot of 32 F rows
+  const int r = w % R, f = w / R;
+  auto part = [&](int x) __attribute__((always_inline)) {
+    // (values, not lvalues: a choice among the members' addresses would put the struct in memory)
+    bf16_t* const a = (x & 1) ? +ring.a1 : +ring.a0;
+    bf16_t* const b = (x & 1) ? +ring.b1 : +ring.b0;
+    bf16_t* const p = (x & 2) ? +b : +a;
+    return reinterpret_cast<float*>(p + (x >> 2) * HALF);
+  };
+#pragma unroll
+  for (int d0 = 0; d0 < D / 32; d0 += ND) {
+    __syncthreads();  // the ring, or the last round's partials, are no longer read
+    float* mine = part(w);
+#pragma unroll
+    for (int d = 0; d < ND; ++d)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<float4*>(mine + ((4 * d + g) * 64 + lane) * 4) =
+            make_float4(acc[d0 + d][4 * g], acc[d0 + d][4 * g + 1], acc[d0 + d][4 * g + 2], acc[d0 + d][4 * g + 3]);
+    __syncthreads();
+#pragma unroll
+    for (int y = 0; y < NU; ++y) {
+      const int u = f * NU + y;
+      float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int x = 0; x < F; ++x) {
+        const float4 t = *reinterpret_cast<const float4*>(part(x * R + r) + (u * 64 + lane) * 4);
+        v[0] += wt[x] * t.x, v[1] += wt[x] * t.y, v[2] += wt[x] * t.z, v[3] += wt[x] * t.w;
+      }
+      out(d0 + u / 4, u % 4, v);
+    }
+  }
+}
+
+__device__ __forceinline__ void store_quad(bf16_t* p, const float* v, float mul) {
+  const uint32_t w0 = (uint32_t)f2bf(v[0] * mul) | ((uint32_t)f2bf(v[1] * mul) << 16);
+  const uint32_t w1 = (uint32_t)f2bf(v[2] * mul) | ((uint32_t)f2bf(v[3] * mul) << 16);
+  *reinterpret_cast<uint2*>(p) = make_uint2(w0, w1);
+}
+
+// ------------------------------------------------------------------ forward
 // IDX: Q, K, V are unused; rows come from the input / pyramid through ix.idx.
-template <int D, bool IDX>
-__global__ void __launch_bounds__(64 * FW) __attribute__((amdgpu_waves_per_eu(LH_FEU, LH_FEU)))
+template <int D, bool IDX, int F>
+__global__ void __launch_bounds__(64 * FwdCfg<F>::NW)
+    __attribute__((amdgpu_waves_per_eu(FwdCfg<F>::EU, FwdCfg<F>::EU)))
 sdpa_fwd_bf16(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
-              bf16_t* __restrict__ O, float* __restrict__ LSE, int S, float sl2, SdpaIdx ix, HeadMap hm) {
-  constexpr int RB = 2 * D;
-  constexpr int NB = FK / 32;  // 32-key blocks per tile
-  constexpr int LPT = 2 * loads_per_wave<D, FK, FW>();
-  static_assert(FNS >= 2 && FNS <= 4, "ring of 2 to 4 slots");
-  LH_RING(bf16_t, Ks, FK * D);
-  LH_RING(bf16_t, Vs, FK * D);
+              bf16_t* __restrict__ O, float* __restrict__ LSE, int S, uint32_t heads, float sl2,
+              SdpaIdx ix, HeadMap hm) {
+  using C = FwdCfg<F>;
+  constexpr int RB = 2 * D, FW = C::NW, FK = C::TILE, FQ = C::ROWS;
+  constexpr int NB = C::NB;  // 32-key blocks of a tile per wave
+  __shared__ __align__(16) bf16_t Ks0[FK * D], Ks1[FK * D], Vs0[FK * D], Vs1[FK * D];
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = lane >> 5, r32 = lane & 31;
-  const BlockPos bp = block_pos();
+  const BlockPos bp = block_pos(blockIdx.x, heads);
   const int64_t bh = bp.head;
   const int nqt = (S + FQ - 1) / FQ;
   const int q0 = (nqt - 1 - bp.rank) * FQ;  // longest rows first
-  const int qw = q0 + 32 * w;
+  const int f = F > 1 ? w / C::R : 0;        // this wave's share of a tile: keys 32 NB f ..
+  const int qw = q0 + 32 * (F > 1 ? w % C::R : w);
   const int myq = qw + r32;
   const int64_t kvh = (bh / hm.Hq) * hm.Hs + (bh % hm.Hq) / hm.Gq;  // selection head
   const bf16_t* Qh = Q + bh * S * D;
   const bf16_t* Kh = K + kvh * S * D;
   const bf16_t* Vh = V + kvh * S * D;
-  const LaneOff<D> lo = lane_offsets<D, LH_SWZ_F>(lane);
+  const LaneOff<D> lo = lane_offsets<D>(lane, 32 * NB * f);
   constexpr int LPW = loads_per_wave<D, FK, FW>();
   RowSrc qsrc{}, ksrc{}, vsrc{};
   const int32_t* idxh = nullptr;
@@ -406,15 +413,15 @@ sdpa_fwd_bf16(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const 
     idxh = ix.idx + kvh * S;
   }
   auto load_kv = [&](int slot_, int r0) __attribute__((always_inline)) {
-    bf16_t* kt_ = slot_ == 0 ? Ks[0] : slot_ == 1 ? Ks[1] : slot_ == 2 ? Ks[2] : Ks[3];
-    bf16_t* vt_ = slot_ == 0 ? Vs[0] : slot_ == 1 ? Vs[1] : slot_ == 2 ? Vs[2] : Vs[3];
+    bf16_t* kt_ = slot_ ? Ks1 : Ks0;
+    bf16_t* vt_ = slot_ ? Vs1 : Vs0;
     if constexpr (IDX) {
-      load_tile_idx<D, FK, FW, LH_SWZ_F>(kt_, ksrc, kv_ids, w, lane);
-      load_tile_idx<D, FK, FW, LH_SWZ_F>(vt_, vsrc, kv_ids, w, lane);
+      load_tile_idx<D, FK, FW>(kt_, ksrc, kv_ids, w, lane);
+      load_tile_idx<D, FK, FW>(vt_, vsrc, kv_ids, w, lane);
       tile_ids<D, FK, FW>(idxh, r0 + FK, S, w, lane, kv_ids);  // the tile after this one
     } else {
-      load_tile<D, FK, FW, LH_SWZ_F>(kt_, Kh, r0, S, w, lane);
-      load_tile<D, FK, FW, LH_SWZ_F>(vt_, Vh, r0, S, w, lane);
+      load_tile<D, FK, FW>(kt_, Kh, r0, S, w, lane);
+      load_tile<D, FK, FW>(vt_, Vh, r0, S, w, lane);
     }
   };
   if constexpr (IDX) tile_ids<D, FK, FW>(idxh, 0, S, w, lane, kv_ids);
@@ -428,42 +435,66 @@ sdpa_fwd_bf16(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const 
     const bf16_t* qr = IDX ? rs_row(qsrc, idxh[qrow]) : Qh + (int64_t)qrow * D;
     qreg[kk] = gld8(qr + 16 * kk + 8 * h);
   }
-#pragma unroll
-  for (int t = 0; t < FNS - 1; ++t) load_kv(t, t * FK);
+  load_kv(0, 0);
   f32x16 oacc[D / 32];
 #pragma unroll
   for (int d = 0; d < D / 32; ++d) oacc[d] = f32x16{};
   float m_run = -INFINITY, l_run = 0.0f;
+  __shared__ float ms[F > 1 ? FW : 1][32], ls[F > 1 ? FW : 1][32];
 
-  auto step = [&](auto slotc, int kt) {
-    constexpr int SL = decltype(slotc)::value;
-    constexpr int NX = (SL + FNS - 1) % FNS;  // slot of tile kt + FNS - 1 (tile kt - 1's)
-    sync_tiles<(FNS - 2) * LPT>();  // tile kt landed in every wave; tile kt - 1 is done
-    load_kv(NX, (kt + FNS - 1) * FK);
-    const int k0 = kt * FK;
-    if (qw + 31 < k0) return;  // every key of the tile is in the future of this wave's rows
-    const bf16_t* Kt = Ks[SL];
-    const bf16_t* Vt = Vs[SL];
-    f32x16 sacc[NB];
+  // S^T = K Q^T of this wave's keys of a tile, masked on the diagonal
+  auto logits = [&](const bf16_t* Kt, int k0, f32x16* sacc) __attribute__((always_inline)) {
 #pragma unroll
     for (int kb = 0; kb < NB; ++kb) sacc[kb] = f32x16{};
 #pragma unroll
     for (int kk = 0; kk < D / 16; ++kk)
 #pragma unroll
       for (int kb = 0; kb < NB; ++kb) sacc[kb] = mfma32(row8(Kt, kb * 32 * RB + lo.row[kk]), qreg[kk], sacc[kb]);
-    if (k0 + FK - 1 > qw) {  // diagonal tile: mask keys after the row
+    if (k0 + 32 * NB - 1 > qw) {  // diagonal tile: mask keys after the row
 #pragma unroll
       for (int kb = 0; kb < NB; ++kb)
 #pragma unroll
         for (int i = 0; i < 16; ++i)
           if (k0 + kb * 32 + 8 * (i >> 2) + 4 * h + (i & 3) > myq) sacc[kb][i] = -INFINITY;
     }
+  };
+  auto row_max = [&](const f32x16* sacc) __attribute__((always_inline)) {  // in log2 units
     float mloc = sacc[0][0];
 #pragma unroll
     for (int kb = 0; kb < NB; ++kb)
 #pragma unroll
       for (int i = 0; i < 16; ++i) mloc = fmaxf(mloc, sacc[kb][i]);
-    mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64)) * sl2;
+    return fmaxf(mloc, __shfl_xor(mloc, 32, 64)) * sl2;
+  };
+  if constexpr (F > 1) {
+    // Every wave starts from the maximum of the row's first 64 keys, as F = 1 does: P is then
+    // rounded to bf16 at the same scale whatever the split (until a maximum grows by 2^8), and a
+    // wave whose own first keys are all masked for a row has a finite maximum.
+    sync_tiles<0>();  // tile 0 has landed
+    if (f < 2) {
+      float mloc = -INFINITY;
+      if (qw + 31 >= 32 * f) {
+        f32x16 sacc[NB];
+        logits(Ks0, 32 * f, sacc);
+        mloc = row_max(sacc);
+      }
+      if (h == 0) ms[w][r32] = mloc;
+    }
+    __syncthreads();
+    m_run = fmaxf(ms[w % C::R][r32], ms[C::R + w % C::R][r32]);
+  }
+
+  auto step = [&](auto slotc, int kt) {
+    constexpr int SL = decltype(slotc)::value;
+    sync_tiles<0>();  // tile kt landed in every wave; tile kt - 1 is done
+    load_kv(SL ^ 1, (kt + 1) * FK);
+    const int k0 = kt * FK + 32 * NB * f;  // this wave's first key of the tile
+    if (qw + 31 < k0) return;  // every key of its share is in the future of this wave's rows
+    const bf16_t* Kt = SL ? Ks1 : Ks0;
+    const bf16_t* Vt = SL ? Vs1 : Vs0;
+    f32x16 sacc[NB];
+    logits(Kt, k0, sacc);
+    const float mloc = row_max(sacc);
     if (mloc > m_run + kRescale) {  // new running maximum: rescale what was accumulated
       const float alpha = __builtin_amdgcn_exp2f(m_run - mloc);
       l_run *= alpha;
@@ -488,13 +519,13 @@ sdpa_fwd_bf16(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const 
     asm volatile("" ::"v"(la), "v"(lb));  // the first step's sums stay ahead of the interleaving
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int st = 0; st < FK / 16; ++st) {
+    for (int st = 0; st < 2 * NB; ++st) {
       bf16x8 pnext = pcur;
-      if (st + 1 < FK / 16) pnext = soft(st + 1);
+      if (st + 1 < 2 * NB) pnext = soft(st + 1);
 #pragma unroll
       for (int d = 0; d < D / 32; ++d)
         oacc[d] = mfma32(tr8(Vt, 16 * st * RB + lo.trl[d], 16 * st * RB + lo.trh[d]), pcur, oacc[d]);
-      if (st + 1 < FK / 16) {
+      if (st + 1 < 2 * NB) {
         // groups: DS reads (mask 0x100), MFMA (0x008), VALU (0x002), transcendental (0x400)
         __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
 #pragma unroll
@@ -510,8 +541,32 @@ sdpa_fwd_bf16(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const 
     }
     l_run += la + lb;
   };
-  for (int t0 = 0; t0 < nkt; t0 += FNS) SlotLoop<0, FNS>::run(t0, nkt, step);
+  for (int t0 = 0; t0 < nkt; t0 += 2) {
+    step(IC<0>{}, t0);
+    if (t0 + 1 < nkt) step(IC<1>{}, t0 + 1);
+  }
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+  if constexpr (F > 1) {
+    sync_tiles<0>();  // the last (unused) tile has landed
+    if (h == 0) ms[w][r32] = m_run, ls[w][r32] = l_tot;
+    __syncthreads();
+    const int r = w % C::R;
+    float M = ms[r][r32], l = 0.0f, wt[F];
+#pragma unroll
+    for (int x = 1; x < F; ++x) M = fmaxf(M, ms[x * C::R + r][r32]);
+#pragma unroll
+    for (int x = 0; x < F; ++x) {
+      wt[x] = __builtin_amdgcn_exp2f(ms[x * C::R + r][r32] - M);  // 0 for a wave without a key of the row
+      l += wt[x] * ls[x * C::R + r][r32];
+    }
+    const float inv = 1.0f / l;
+    bf16_t* orow = O + (bh * S + myq) * D;
+    combine<D, F, C::R>(Ring<0>{Ks0, Ks1, Vs0, Vs1}, oacc, wt, w, lane, [&](int d, int g, const float* v) {
+      if (myq < S) store_quad(orow + 32 * d + 8 * g + 4 * h, v, inv);
+    });
+    if (myq < S && f == 0 && h == 0) LSE[bh * S + myq] = (M + __log2f(l)) * kLn2;
+    return;
+  }
   if (myq < S) {
     store_qrow<D>(O + (bh * S + myq) * D, oacc, 1.0f / l_tot, h);
     if (h == 0) LSE[bh * S + myq] = (m_run + __log2f(l_tot)) * kLn2;
@@ -522,32 +577,28 @@ sdpa_fwd_bf16(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const 
 // Each wave owns 32 query rows (their Q and dO rows stay in registers) and streams the K/V
 // tiles: S^T = K Q^T and dP^T = V dO^T give, per lane, one query row's
 // P = exp2(S scale log2e - lse log2e) and dS = P (dP - Delta); dQ^T += K^T dS^T.
-constexpr int QW = LH_QW, BQ = 32 * LH_QW, BK = LH_BK, QNS = LH_QNS;
-
-template <int D, bool IDX>
-__global__ void __launch_bounds__(64 * QW) __attribute__((amdgpu_waves_per_eu(2, 2)))
-sdpa_bwd_dq_bf16(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
-                 const bf16_t* __restrict__ dO, const float* __restrict__ LSE, const float* __restrict__ DELTA,
-                 bf16_t* __restrict__ dQ, int S, float sl2, float scale, SdpaIdx ix, HeadMap hm) {
-  constexpr int RB = 2 * D;
-  constexpr int LPT = 2 * loads_per_wave<D, BK, QW>();
-  static_assert(QNS >= 2 && QNS <= 4, "ring of 2 to 4 slots");
-  LH_RING(bf16_t, Ks, BK * D);
-  LH_RING(bf16_t, Vs, BK * D);
+template <int D, bool IDX, int F>
+__device__ __forceinline__ void
+dq_block(const BlockPos bp, const Ring<0> ring, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
+         const bf16_t* __restrict__ V, const bf16_t* __restrict__ dO, const float* __restrict__ LSE,
+         const float* __restrict__ DELTA, bf16_t* __restrict__ dQ, int S, float sl2, float scale, const SdpaIdx& ix,
+         const HeadMap& hm) {
+  using C = BwdCfg<F>;
+  constexpr int RB = 2 * D, QW = C::NW, BQ = C::ROWS, BK = C::TILE;
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = lane >> 5, r32 = lane & 31;
-  const BlockPos bp = block_pos();
   const int64_t bh = bp.head;
   const int nqt = (S + BQ - 1) / BQ;
   const int q0 = (nqt - 1 - bp.rank) * BQ;
-  const int qw = q0 + 32 * w;
+  const int f = kSplitAt<IDX, F> ? w / C::R : 0;
+  const int qw = q0 + 32 * (kSplitAt<IDX, F> ? w % C::R : w);
   const int myq = qw + r32;
   const int64_t kvh = (bh / hm.Hq) * hm.Hs + (bh % hm.Hq) / hm.Gq;  // selection head
   const bf16_t* Qh = Q + bh * S * D;
   const bf16_t* Kh = K + kvh * S * D;
   const bf16_t* Vh = V + kvh * S * D;
   const bf16_t* dOh = dO + bh * S * D;
-  const LaneOff<D> lo = lane_offsets<D, LH_SWZ_Q>(lane);
+  const LaneOff<D> lo = lane_offsets<D>(lane, 32 * C::NB * f);
   constexpr int LPW = loads_per_wave<D, BK, QW>();
   RowSrc qsrc{}, ksrc{}, vsrc{};
   const int32_t* idxh = nullptr;
@@ -562,15 +613,15 @@ sdpa_bwd_dq_bf16(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, con
     tile_ids<D, BK, QW>(idxh, 0, S, w, lane, kv_ids);
   }
   auto load_kv = [&](int slot_, int r0) __attribute__((always_inline)) {
-    bf16_t* kt_ = slot_ == 0 ? Ks[0] : slot_ == 1 ? Ks[1] : slot_ == 2 ? Ks[2] : Ks[3];
-    bf16_t* vt_ = slot_ == 0 ? Vs[0] : slot_ == 1 ? Vs[1] : slot_ == 2 ? Vs[2] : Vs[3];
+    bf16_t* kt_ = slot_ ? ring.a1 : ring.a0;
+    bf16_t* vt_ = slot_ ? ring.b1 : ring.b0;
     if constexpr (IDX) {
-      load_tile_idx<D, BK, QW, LH_SWZ_Q>(kt_, ksrc, kv_ids, w, lane);
-      load_tile_idx<D, BK, QW, LH_SWZ_Q>(vt_, vsrc, kv_ids, w, lane);
+      load_tile_idx<D, BK, QW>(kt_, ksrc, kv_ids, w, lane);
+      load_tile_idx<D, BK, QW>(vt_, vsrc, kv_ids, w, lane);
       tile_ids<D, BK, QW>(idxh, r0 + BK, S, w, lane, kv_ids);
     } else {
-      load_tile<D, BK, QW, LH_SWZ_Q>(kt_, Kh, r0, S, w, lane);
-      load_tile<D, BK, QW, LH_SWZ_Q>(vt_, Vh, r0, S, w, lane);
+      load_tile<D, BK, QW>(kt_, Kh, r0, S, w, lane);
+      load_tile<D, BK, QW>(vt_, Vh, r0, S, w, lane);
     }
   };
 
@@ -592,27 +643,24 @@ sdpa_bwd_dq_bf16(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, con
   f32x16 ndlt;
 #pragma unroll
   for (int i = 0; i < 16; ++i) ndlt[i] = -dlt;
-#pragma unroll
-  for (int t = 0; t < QNS - 1; ++t) load_kv(t, t * BK);
+  load_kv(0, 0);
   f32x16 dqacc[D / 32];
 #pragma unroll
   for (int d = 0; d < D / 32; ++d) dqacc[d] = f32x16{};
 
-  // Key tiles before q0 hold no key after any row of the block: no mask. Only the last
-  // BQ / BK tiles (the diagonal band) run the masked body.
-  static_assert(QNS == 2, "the masked / unmasked split runs a two-slot ring");
+  // Key tiles that end before q0 hold no key after any row of the block: no mask. Only the last
+  // tiles (the diagonal band) run the masked body.
   auto step = [&](auto slotc, auto maskc, int kt) __attribute__((always_inline)) {
     constexpr int SL = decltype(slotc)::value;
     constexpr bool MASK = decltype(maskc)::value != 0;
-    constexpr int NX = (SL + QNS - 1) % QNS;
-    sync_tiles<(QNS - 2) * LPT>();
-    load_kv(NX, (kt + QNS - 1) * BK);
-    const int k0 = kt * BK;
+    sync_tiles<0>();
+    load_kv(SL ^ 1, (kt + 1) * BK);
+    const int k0 = kt * BK + 32 * C::NB * f;  // this wave's first key of the tile
     if (qw + 31 < k0) return;
-    const bf16_t* Kt = Ks[SL];
-    const bf16_t* Vt = Vs[SL];
+    const bf16_t* Kt = ring.a<SL>();
+    const bf16_t* Vt = ring.b<SL>();
 #pragma unroll
-    for (int kb = 0; kb < BK / 32; ++kb) {
+    for (int kb = 0; kb < C::NB; ++kb) {
       f32x16 sacc = f32x16{};
       f32x16 pacc = mfma32(row8(Vt, kb * 32 * RB + lo.row[0]), doreg[0], ndlt);
 #pragma unroll
@@ -646,7 +694,18 @@ sdpa_bwd_dq_bf16(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, con
   auto masked = [&](auto slotc, int kt) __attribute__((always_inline)) { step(slotc, IC<1>{}, kt); };
   ring2_loop(0, nfree, plain);
   ring2_loop(nfree, nkt, masked);
-  if (myq < S) store_qrow<D>(dQ + (bh * S + myq) * D, dqacc, scale, h);
+  if constexpr (F > 1) {
+    float one[F];
+#pragma unroll
+    for (int x = 0; x < F; ++x) one[x] = 1.0f;
+    sync_tiles<0>();  // the last (unused) tile has landed
+    bf16_t* row = dQ + (bh * S + myq) * D;
+    combine<D, F, C::R>(ring, dqacc, one, w, lane, [&](int d, int g, const float* v) {
+      if (myq < S) store_quad(row + 32 * d + 8 * g + 4 * h, v, scale);
+    });
+  } else {
+    if (myq < S) store_qrow<D>(dQ + (bh * S + myq) * D, dqacc, scale, h);
+  }
 }
 
 // ------------------------------------------------------------------ backward: dK, dV
@@ -656,33 +715,27 @@ sdpa_bwd_dq_bf16(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, con
 // dK += dS^T Q with the transposed dO / Q operands read from the same tiles. Each query tile
 // is processed in two 32-row halves to bound the live registers. The lse / Delta of a tile
 // pass through registers, so each step waits for all of the wave's loads before the barrier.
-constexpr int KWV = LH_KWV, CK = 32 * LH_KWV, CQ = LH_CQ;
-static_assert(CQ % 32 == 0 && CQ <= 64, "query tile of 32 or 64 rows");
-
 // GRP: the workgroup's keys belong to a selection shared by hm.Gq query heads; their dK, dV sum
 // over those heads (one pass of the query-tile loop per head, the accumulators kept).
-template <int D, bool IDX, bool GRP>
-__global__ void __launch_bounds__(64 * KWV) __attribute__((amdgpu_waves_per_eu(LH_KWV_EU, LH_KWV_EU)))
-sdpa_bwd_dkdv_bf16(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
-                   const bf16_t* __restrict__ dO, const float* __restrict__ LSE, const float* __restrict__ DELTA,
-                   bf16_t* __restrict__ dK, bf16_t* __restrict__ dV, int S, float sl2, float scale, SdpaIdx ix,
-                   HeadMap hm) {
-  constexpr int RB = 2 * D;
-  // LDS is laid out by decreasing alignment: the lse / Delta rows (1 KB) first, then the query
-  // tiles, so that both sit inside the first 64 KB, where a base address folds into the 16-bit
-  // immediate offset of the LDS reads (the deepest tile read ends below 63 KB); K comes last.
-  __shared__ __align__(128) float ls0[CQ], ls1[CQ], ds0[CQ], ds1[CQ];
-  __shared__ __align__(64) bf16_t Qs0[CQ * D], Qs1[CQ * D], dOs0[CQ * D], dOs1[CQ * D];
-  __shared__ __align__(16) bf16_t Kw[CK * D];
+template <int D, bool IDX, bool GRP, int F>
+__device__ __forceinline__ void
+dkdv_block(const BlockPos bp, const Ring<0> ring, float* const ls0, float* const ls1, float* const ds0,
+           float* const ds1, bf16_t* const Kw, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
+           const bf16_t* __restrict__ V, const bf16_t* __restrict__ dO, const float* __restrict__ LSE,
+           const float* __restrict__ DELTA, bf16_t* __restrict__ dK, bf16_t* __restrict__ dV, int S, float sl2,
+           float scale, const SdpaIdx& ix, const HeadMap& hm) {
+  using C = BwdCfg<F>;
+  constexpr int RB = 2 * D, KWV = C::NW, CK = C::ROWS, CQ = C::TILE;
+  bf16_t *const Qs0 = ring.a0, *const Qs1 = ring.a1, *const dOs0 = ring.b0, *const dOs1 = ring.b1;
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = lane >> 5, r32 = lane & 31;
-  const BlockPos bp = block_pos();
   const int64_t bs = bp.head;  // b * Hs + hs: the selection head whose keys this block owns
   const int64_t bsb = bs / hm.Hs;
   const int hs0 = (int)(bs - bsb * hm.Hs);
   int64_t bh = bsb * hm.Hq + (int64_t)hs0 * hm.Gq;  // the query head being streamed
   const int k0 = bp.rank * CK;  // early keys see the most queries: launched first
-  const int kw = k0 + 32 * w;
+  const int r = kSplitAt<IDX, F> ? w % C::R : w, f = kSplitAt<IDX, F> ? w / C::R : 0;
+  const int kw = k0 + 32 * r;
   const int mykey = kw + r32;
   const bf16_t* Qh = Q + bh * S * D;
   const bf16_t* Kh = K + bs * S * D;
@@ -690,7 +743,9 @@ sdpa_bwd_dkdv_bf16(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, c
   const bf16_t* dOh = dO + bh * S * D;
   const float* Lh = LSE + bh * S;
   const float* Dh = DELTA + bh * S;
-  const LaneOff<D> lo = lane_offsets<D, LH_SWZ_K>(lane);
+  const LaneOff<D> lo = lane_offsets<D>(lane, 32 * C::NB * f);
+  // the K operand's row block is r, not the tile share f
+  const int kwo = (r - C::NB * f) * 32 * RB;
   RowSrc qsrc{}, ksrc{}, vsrc{};
   const int32_t* idxh = nullptr;
   int32_t q_ids[loads_per_wave<D, CQ, KWV>()];  // ids of the next query tile to be staged
@@ -717,9 +772,9 @@ sdpa_bwd_dkdv_bf16(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, c
   };
   auto stage = [&](auto bufc, auto deferc, int qt0) __attribute__((always_inline)) {
     constexpr int BUF = decltype(bufc)::value;
-    if constexpr (IDX) load_tile_idx<D, CQ, KWV, LH_SWZ_K>(BUF ? Qs1 : Qs0, qsrc, q_ids, w, lane);
-    else load_tile<D, CQ, KWV, LH_SWZ_K>(BUF ? Qs1 : Qs0, Qh, qt0, S, w, lane);
-    load_tile<D, CQ, KWV, LH_SWZ_K>(BUF ? dOs1 : dOs0, dOh, qt0, S, w, lane);
+    if constexpr (IDX) load_tile_idx<D, CQ, KWV>(BUF ? Qs1 : Qs0, qsrc, q_ids, w, lane);
+    else load_tile<D, CQ, KWV>(BUF ? Qs1 : Qs0, Qh, qt0, S, w, lane);
+    load_tile<D, CQ, KWV>(BUF ? dOs1 : dOs0, dOh, qt0, S, w, lane);
     if (tid < CQ) {
       const int q = qt0 + tid < S ? qt0 + tid : S - 1;  // clamped; rows past S are masked in put_ld
       if constexpr (decltype(deferc)::value) {
@@ -739,10 +794,10 @@ sdpa_bwd_dkdv_bf16(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, c
   if constexpr (IDX) {
     int32_t k_ids[loads_per_wave<D, CK, KWV>()];
     tile_ids<D, CK, KWV>(idxh, k0, S, w, lane, k_ids);
-    load_tile_idx<D, CK, KWV, LH_SWZ_K>(Kw, ksrc, k_ids, w, lane);
+    load_tile_idx<D, CK, KWV>(Kw, ksrc, k_ids, w, lane);
     tile_ids<D, CQ, KWV>(idxh, qlast, S, w, lane, q_ids);
   } else {
-    load_tile<D, CK, KWV, LH_SWZ_K>(Kw, Kh, k0, S, w, lane);
+    load_tile<D, CK, KWV>(Kw, Kh, k0, S, w, lane);
   }
   stage(IC<0>{}, IC<0>{}, qlast);
 
@@ -760,18 +815,19 @@ sdpa_bwd_dkdv_bf16(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, c
     constexpr bool MASK = decltype(maskc)::value != 0;
     const bf16_t* Qt = BUF ? Qs1 : Qs0;
     const bf16_t* dOt = BUF ? dOs1 : dOs0;
-    const float* lt = BUF ? ls1 : ls0;
-    const float* dt = BUF ? ds1 : ds0;
     const int qt0 = qlast - it * CQ;
     if (it > 0 && tid < CQ) put_ld(bufc, qt0, nl, nd);  // staged with the previous tile
     sync_tiles<0>();  // this tile (and its lse / Delta) landed; the other slot is free
     if (it + 1 < nqt) stage(IC<BUF ^ 1>{}, IC<1>{}, qt0 - CQ);
-    if (qt0 + CQ - 1 < kw || kw >= S) return;  // every query of the tile precedes this wave's keys
+    const int qs0 = qt0 + 32 * C::NB * f;  // this wave's first query of the tile
+    if (qs0 + 32 * C::NB - 1 < kw || kw >= S) return;  // every query of its share precedes its keys
+    const float* lt = (BUF ? ls1 : ls0) + 32 * C::NB * f;
+    const float* dt = (BUF ? ds1 : ds0) + 32 * C::NB * f;
 #pragma unroll
-    for (int qb = 0; qb < CQ / 32; ++qb) {
-      // causal mask: element i holds query row qt0 + 32 qb + 4h + c_i, c_i = 8 (i / 4) + i % 4, so
+    for (int qb = 0; qb < C::NB; ++qb) {
+      // causal mask: element i holds query row qs0 + 32 qb + 4h + c_i, c_i = 8 (i / 4) + i % 4, so
       // P = 0 exactly where c_i < t (t < 0 on every tile after this wave's diagonal one)
-      const int tmask = mykey - qt0 - 32 * qb - 4 * h;
+      const int tmask = mykey - qs0 - 32 * qb - 4 * h;
       // the dP accumulator starts at -Delta (stored negated), so it ends as dP - Delta
       f32x16 sacc = f32x16{}, pacc;
 #pragma unroll
@@ -781,7 +837,7 @@ sdpa_bwd_dkdv_bf16(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, c
       }
 #pragma unroll
       for (int kk = 0; kk < D / 16; ++kk) {
-        sacc = mfma32(row8(Qt, qb * 32 * RB + lo.row[kk]), row8(Kw, w * 32 * RB + lo.row[kk]), sacc);
+        sacc = mfma32(row8(Qt, qb * 32 * RB + lo.row[kk]), row8(Kw, kwo + lo.row[kk]), sacc);
         pacc = mfma32(row8(dOt, qb * 32 * RB + lo.row[kk]), vreg[kk], pacc);
         if (kk & 1) __builtin_amdgcn_sched_barrier(0);  // bound the operand loads in flight
       }
@@ -816,8 +872,9 @@ sdpa_bwd_dkdv_bf16(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, c
     }
   };
   // Query tiles at or after k0 + CK hold no query before any key of the block: no mask. Only the
-  // last CK / CQ tiles visited (the diagonal band) run the masked body.
-  const int nfree = nqt > CK / CQ ? nqt - CK / CQ : 0;
+  // last tiles visited (the diagonal band) run the masked body.
+  constexpr int NMASK = CK > CQ ? CK / CQ : 1;
+  const int nfree = nqt > NMASK ? nqt - NMASK : 0;
   auto plain = [&](auto bufc, int it) __attribute__((always_inline)) { tile(bufc, IC<0>{}, it); };
   auto masked = [&](auto bufc, int it) __attribute__((always_inline)) { tile(bufc, IC<1>{}, it); };
   for (int mq = 0;;) {
@@ -839,65 +896,158 @@ sdpa_bwd_dkdv_bf16(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, c
     stage(IC<0>{}, IC<0>{}, qlast);
   }
   // C layout: row = key kw + 8(i/4) + 4h + i%4, column 32 d + lane % 32
+  if constexpr (F > 1) {
+    float one[F];
 #pragma unroll
-  for (int d = 0; d < D / 32; ++d)
+    for (int x = 0; x < F; ++x) one[x] = 1.0f;
+    auto put = [&](bf16_t* dst, float mul) __attribute__((always_inline)) {
+      return [=](int d, int g, const float* v) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int key = kw + 8 * (i >> 2) + 4 * h + (i & 3);
-      if (key < S) {
-        dK[(bs * S + key) * D + 32 * d + r32] = f2bf(dkacc[d][i] * scale);
-        dV[(bs * S + key) * D + 32 * d + r32] = f2bf(dvacc[d][i]);
+        for (int j = 0; j < 4; ++j) {
+          const int key = kw + 8 * g + 4 * h + j;
+          if (key < S) dst[(bs * S + key) * D + 32 * d + r32] = f2bf(v[j] * mul);
+        }
+      };
+    };
+    combine<D, F, C::R>(ring, dkacc, one, w, lane, put(dK, scale));
+    combine<D, F, C::R>(ring, dvacc, one, w, lane, put(dV, 1.0f));
+  } else {
+#pragma unroll
+    for (int d = 0; d < D / 32; ++d)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int key = kw + 8 * (i >> 2) + 4 * h + (i & 3);
+        if (key < S) {
+          dK[(bs * S + key) * D + 32 * d + r32] = f2bf(dkacc[d][i] * scale);
+          dV[(bs * S + key) * D + 32 * d + r32] = f2bf(dvacc[d][i]);
+        }
       }
-    }
+  }
+}
+
+// ------------------------------------------------------------------ backward: the launch
+// dK/dV and dQ workgroups in one launch: they are independent and of one shape (8 waves, one
+// workgroup per CU at D = 128), so the long dQ blocks fill the CUs that the last dK/dV blocks
+// leave idle. Against two launches, F = 1: S = 2000, 8 heads 169 -> 103 us; 18,432, 8 heads 2161
+// -> 2065; 10,752, 32 heads on 8 selections 3477 -> 2910; no difference on a full chip (54,272, 32
+// heads). Alternating the ranks of dK/dV and dQ blocks instead of all dK/dV first was slower
+// (18,432, 8 heads 2269): the blocks running together then stream more different tiles through
+// each L2. LDS is shared by name: dQ's K / V ring is dK/dV's Q / dO ring.
+struct BwdArgs {
+  const bf16_t *q, *k, *v, *go;
+  const float *lse, *delta;
+  bf16_t *dq, *dk, *dv;
+  int S;
+  uint32_t kheads, qheads;  // heads of dK/dV and of dQ blocks
+  uint32_t kblocks;         // dK/dV blocks, the first of the launch
+  float sl2, scale;
+};
+
+template <int D, bool IDX, bool GRP, int F>
+__global__ void __launch_bounds__(64 * BwdCfg<F>::NW)
+    __attribute__((amdgpu_waves_per_eu(BwdCfg<F>::EU, BwdCfg<F>::EU)))
+sdpa_bwd_bf16(BwdArgs a, SdpaIdx ix, HeadMap hm) {
+  using C = BwdCfg<F>;
+  constexpr int CQ = C::TILE, CK = C::ROWS;
+  // LDS is laid out by decreasing alignment: the lse / Delta rows first, then the streamed tiles,
+  // so that with F < 4 both sit inside the first 64 KB, where a base address folds into the
+  // 16-bit immediate offset of the LDS reads (the deepest tile read ends below 63 KB); K comes last.
+  __shared__ __align__(128) float ls0[CQ], ls1[CQ], ds0[CQ], ds1[CQ];
+  __shared__ __align__(64) bf16_t A0[CQ * D], A1[CQ * D], B0[CQ * D], B1[CQ * D];
+  __shared__ __align__(16) bf16_t Kw[CK * D];
+  const uint32_t lin = blockIdx.x;
+  const Ring<0> ring{A0, A1, B0, B1};
+  if (lin < a.kblocks)
+    dkdv_block<D, IDX, GRP, F>(block_pos(lin, a.kheads), ring, ls0, ls1, ds0, ds1, Kw, a.q, a.k, a.v, a.go, a.lse,
+                               a.delta, a.dk, a.dv, a.S, a.sl2, a.scale, ix, hm);
+  else
+    dq_block<D, IDX, F>(block_pos(lin - a.kblocks, a.qheads), ring, a.q, a.k, a.v, a.go, a.lse, a.delta, a.dq, a.S, a.sl2,
+                        a.scale, ix, hm);
+}
+
+// The split F of a launch (FwdCfg, BwdCfg) by the number of 32-row blocks of all heads, from
+// sweeps of S = 100 .. 30,000 rows and 2 .. 32 heads at D = 64 and 128 (the lines are the same).
+// Forward: a block of F = 1 needs 2.2 us per 64 keys (D = 128), F = 2 1.06 us, F = 4 1.47 us per
+// 128; a full chip does 2.1, 1.8 and 1.4 G pairs per ms. At 1248 blocks (S = 5000, 8 heads) F = 1,
+// 2, 4 take 174, 92, 95 us; at 768 (3000, 8) 110, 58, 43; at 3000 (12,000, 8) 422, 360, 420; at
+// 4608 (18,432, 8) 726, 761, 934.
+static int fwd_split(const LhShape& s) {
+  const int64_t nb = (s.S + 31) / 32 * s.B * s.Hq;
+  return nb <= 1280 ? 4 : nb <= 3400 ? 2 : 1;
+}
+// Backward (dK/dV and dQ together): at 504 blocks (S = 2000, 8 heads) 103, 70, 60 us; at 752
+// (3000, 8) 148, 101, 109; at 1248 (5000, 8) 251, 204, 236; at 1500 (3000, 16) 165, 173, 220. With
+// a shared selection a dK/dV block is Gq times as long, so the lines lie further out: at 672
+// blocks of 4 query heads each (10,752 rows, 2 selections) 1940, 1153, 968; at 1344 (10,752, 4)
+// 2192, 1621, 1841; at 2304 (18,432, 4) 4434, 4708, 5330.
+static int bwd_split(const LhShape& s) {
+  const int64_t nb = (s.S + 31) / 32 * s.B * s.Hs;
+  if (s.Gq > 1) return nb <= 800 ? 4 : nb <= 2100 ? 2 : 1;
+  return nb <= 560 ? 4 : nb <= 1450 ? 2 : 1;
+}
+
+template <int D, bool IDX, int F>
+static void launch_fwd_F(const LhShape& s, const void* qs, const void* ks, const void* vs, void* os, float* lse,
+                         const SdpaIdx& ix, hipStream_t st) {
+  using C = FwdCfg<F>;
+  const int S = (int)s.S;
+  const HeadMap hm{s.Hq, s.Hs, s.Gq};
+  const uint32_t heads = (uint32_t)(s.B * s.Hq);
+  const dim3 grid((uint32_t)((s.S + C::ROWS - 1) / C::ROWS) * heads);
+  hipLaunchKernelGGL((sdpa_fwd_bf16<D, IDX, F>), grid, dim3(64 * C::NW), 0, st, (const bf16_t*)qs, (const bf16_t*)ks,
+                     (const bf16_t*)vs, (bf16_t*)os, lse, S, heads, s.scale * kLog2e, ix, hm);
+}
+
+template <int D, bool IDX>
+static void launch_fwd_D(const LhShape& s, const void* qs, const void* ks, const void* vs, void* os, float* lse,
+                         const SdpaIdx& ix, hipStream_t st) {
+  switch (fwd_split(s)) {
+    case 1: launch_fwd_F<D, IDX, 1>(s, qs, ks, vs, os, lse, ix, st); break;
+    case 2: launch_fwd_F<D, IDX, 2>(s, qs, ks, vs, os, lse, ix, st); break;
+    default: launch_fwd_F<D, IDX, 4>(s, qs, ks, vs, os, lse, ix, st); break;
+  }
 }
 
 template <bool IDX>
 static void launch_fwd(const LhShape& s, const void* qs, const void* ks, const void* vs, void* os, float* lse,
                        const SdpaIdx& ix, hipStream_t st) {
-  const int S = (int)s.S;
+  if (s.D == 128) launch_fwd_D<128, IDX>(s, qs, ks, vs, os, lse, ix, st);
+  else launch_fwd_D<64, IDX>(s, qs, ks, vs, os, lse, ix, st);
+}
+
+template <int D, bool IDX, bool GRP, int F>
+static void launch_bwd_F(const LhShape& s, BwdArgs a, const SdpaIdx& ix, hipStream_t st) {
+  using C = BwdCfg<F>;
   const HeadMap hm{s.Hq, s.Hs, s.Gq};
-  dim3 grid((unsigned)((S + FQ - 1) / FQ), (unsigned)(s.B * s.Hq));
-  const float sl2 = s.scale * kLog2e;
-  auto q = (const bf16_t*)qs;
-  auto k = (const bf16_t*)ks;
-  auto v = (const bf16_t*)vs;
-  if (s.D == 128)
-    hipLaunchKernelGGL((sdpa_fwd_bf16<128, IDX>), grid, dim3(64 * FW), 0, st, q, k, v, (bf16_t*)os, lse, S, sl2, ix,
-                       hm);
-  else
-    hipLaunchKernelGGL((sdpa_fwd_bf16<64, IDX>), grid, dim3(64 * FW), 0, st, q, k, v, (bf16_t*)os, lse, S, sl2, ix, hm);
+  const uint32_t n = (uint32_t)((s.S + C::ROWS - 1) / C::ROWS);
+  a.kblocks = n * a.kheads;
+  const dim3 grid(a.kblocks + n * a.qheads);
+  hipLaunchKernelGGL((sdpa_bwd_bf16<D, IDX, GRP, F>), grid, dim3(64 * C::NW), 0, st, a, ix, hm);
 }
 
 template <int D, bool IDX, bool GRP>
-static void launch_bwd_D(const LhShape& s, const bf16_t* q, const bf16_t* k, const bf16_t* v, const bf16_t* g,
-                         const float* lse, const float* delta, void* dqs, void* dks, void* dvs, const SdpaIdx& ix,
-                         hipStream_t st) {
-  const int S = (int)s.S;
-  const float sl2 = s.scale * kLog2e;
-  const HeadMap hm{s.Hq, s.Hs, s.Gq};
-  dim3 gk((unsigned)((S + CK - 1) / CK), (unsigned)(s.B * s.Hs));  // per (key block, selection head)
-  dim3 gq((unsigned)((S + BQ - 1) / BQ), (unsigned)(s.B * s.Hq));
-  hipLaunchKernelGGL((sdpa_bwd_dkdv_bf16<D, IDX, GRP>), gk, dim3(64 * KWV), 0, st, q, k, v, g, lse, delta,
-                     (bf16_t*)dks, (bf16_t*)dvs, S, sl2, s.scale, ix, hm);
-  hipLaunchKernelGGL((sdpa_bwd_dq_bf16<D, IDX>), gq, dim3(64 * QW), 0, st, q, k, v, g, lse, delta, (bf16_t*)dqs, S,
-                     sl2, s.scale, ix, hm);
+static void launch_bwd_D(const LhShape& s, const BwdArgs& a, const SdpaIdx& ix, hipStream_t st) {
+  switch (bwd_split(s)) {
+    case 1: launch_bwd_F<D, IDX, GRP, 1>(s, a, ix, st); break;
+    case 2: launch_bwd_F<D, IDX, GRP, 2>(s, a, ix, st); break;
+    default: launch_bwd_F<D, IDX, GRP, 4>(s, a, ix, st); break;
+  }
 }
 
 template <bool IDX>
 static void launch_bwd(const LhShape& s, const void* qs, const void* ks, const void* vs, const void* dos,
                        const float* lse, const float* delta, void* dqs, void* dks, void* dvs, const SdpaIdx& ix,
                        hipStream_t st) {
-  auto q = (const bf16_t*)qs;
-  auto k = (const bf16_t*)ks;
-  auto v = (const bf16_t*)vs;
-  auto g = (const bf16_t*)dos;
+  const BwdArgs a{(const bf16_t*)qs, (const bf16_t*)ks, (const bf16_t*)vs, (const bf16_t*)dos, lse, delta,
+                  (bf16_t*)dqs, (bf16_t*)dks, (bf16_t*)dvs, (int)s.S, (uint32_t)(s.B * s.Hs),
+                  (uint32_t)(s.B * s.Hq), 0, s.scale * kLog2e, s.scale};
   const bool grp = s.Gq > 1;
   if (s.D == 128) {
-    if (grp) launch_bwd_D<128, IDX, true>(s, q, k, v, g, lse, delta, dqs, dks, dvs, ix, st);
-    else launch_bwd_D<128, IDX, false>(s, q, k, v, g, lse, delta, dqs, dks, dvs, ix, st);
+    if (grp) launch_bwd_D<128, IDX, true>(s, a, ix, st);
+    else launch_bwd_D<128, IDX, false>(s, a, ix, st);
   } else {
-    if (grp) launch_bwd_D<64, IDX, true>(s, q, k, v, g, lse, delta, dqs, dks, dvs, ix, st);
-    else launch_bwd_D<64, IDX, false>(s, q, k, v, g, lse, delta, dqs, dks, dvs, ix, st);
+    if (grp) launch_bwd_D<64, IDX, true>(s, a, ix, st);
+    else launch_bwd_D<64, IDX, false>(s, a, ix, st);
   }
 }
 

@@ -69,3 +69,53 @@ def test_fp32_shared(S, D, Hq, rng):
     """dK, dV over the query heads of a shared selection; at (545, 64, 32) the row blocks fill the
     chip and the 4-wave split runs at D = 64."""
     run_case(S, D, "fp32", Hq, 2, True, rng, heads=[0] if Hq > 8 else None)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("S", [1, 33, 64, 65, 127, 128, 129, 257])
+def test_bf16_few_blocks(S, D, rng):
+    """Few row blocks: a workgroup owns 64 rows, each 32-row block shared by 4 waves that take 32
+    rows each of every 128-row tile."""
+    run_case(S, D, "bf16", 2, 2, False, rng)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("S,Hq,Hkv", [(1313, 32, 32), (1377, 80, 80), (161, 4, 2), (1313, 40, 20), (1377, 96, 48)])
+def test_bf16_splits(S, Hq, Hkv, D, rng):
+    """Row block counts on which the forward and the backward share a row block by 2 waves
+    (42 * 32 blocks) and by none (44 * 80); with shared selections the backward by 4 (6 * 2), 2
+    (42 * 20) and none (44 * 48)."""
+    run_case(S, D, "bf16", Hq, Hkv, Hkv != Hq, rng, heads=[0] if Hkv > 2 else None)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("S,Hq,Hkv", [(321, 4, 4), (1313, 32, 32), (1377, 80, 80), (161, 4, 2), (1313, 40, 20), (1377, 96, 48)])
+def test_indexed_equals_gathered(S, Hq, Hkv, D):
+    """The index-driven kernels give the bits of the gather followed by the plain ones, whichever
+    split runs (rows in any order, some taken twice)."""
+    print(f"[sdpa edges indexed] S={S} D={D} Hq={Hq} Hkv={Hkv}", flush=True)
+    shared = Hkv != Hq
+    pr = lh.problem(1, S, Hq, Hkv, D, 2, 1, 0, torch.bfloat16, flags=lh.LH_FLAG_GQA_SHARED if shared else 0)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(S + D)
+    new = lambda *s: torch.randn(*s, device=DEV, generator=g).to(torch.bfloat16)  # noqa: E731
+    q, k, v = new(1, S, Hq, D), new(1, S, Hkv, D), new(1, S, Hkv, D)
+    idx = torch.randint(0, S, (1, Hkv, S), device=DEV, generator=g).to(torch.int32)
+    qs, ks, vs, dos = new(1, Hq, S, D), new(1, Hkv, S, D), new(1, Hkv, S, D), new(1, Hq, S, D)
+    lh.lh_gather(pr, q, k, v, None, None, None, idx, qs, ks, vs)
+    ws = lh.workspace(pr, lh.LH_OP_SDPA_BWD)
+    got = []
+    for indexed in (False, True):
+        o, dqs, dks, dvs = (torch.full_like(t, float("nan")) for t in (qs, qs, ks, vs))
+        lse = torch.empty(1, Hq, S, device=DEV)
+        if indexed:
+            lh.lh_sdpa_fwd_indexed(pr, q, k, v, None, None, None, idx, o, lse)
+            lh.lh_sdpa_bwd_indexed(pr, q, k, v, None, None, None, idx, o, lse, dos, dqs, dks, dvs, ws)
+        else:
+            lh.lh_sdpa_fwd(pr, qs, ks, vs, o, lse)
+            lh.lh_sdpa_bwd(pr, qs, ks, vs, o, lse, dos, dqs, dks, dvs, ws)
+        got.append((o, lse, dqs, dks, dvs))
+    torch.cuda.synchronize()
+    for name, a, b in zip(("os", "lse", "dqs", "dks", "dvs"), *got):
+        assert torch.equal(a.view(torch.int16 if a.dtype == torch.bfloat16 else torch.int32),
+                           b.view(torch.int16 if b.dtype == torch.bfloat16 else torch.int32)), name
