@@ -481,3 +481,94 @@ def test_order_ranges_match_sorted_keys(N, p, L, k, replace, seed):
     emitted.sort()
     want = {(l, i): r for r, (_, l, i) in enumerate(emitted)}
     assert got == want
+
+
+# ---------------------------------------------------------------- pool_leaf_kernel (p = 2, 3, 4)
+
+def _leaf_launch(s, A, BR):
+    """launch_leaf: (LR, HW, RG, WR, threads, LDS bytes), or None where it declines."""
+    P_, LR, CPR = s.p, s.p ** A, 1 << s.cs
+    nslots = s.Hq + 2 * s.Hkv
+    rg_min = max(s.P // LR, 1)
+    if rg_min * CPR > 1024:
+        return None
+    sh = 0
+    for t in range(1, 5):
+        hw = 1 << t
+        if rg_min * CPR * hw <= 256 and -(-nslots // hw) * hw * 8 <= nslots * 9:
+            sh = t
+    unit = rg_min * CPR << sh
+    RG = rg_min * (1 if unit >= 256 else 256 // unit)
+    WR, HW = RG * LR, 1 << sh
+    nt = RG * CPR << sh
+    staged = RG * HW * BR * (s.D * s.es + 16)
+    sums = nt * s.CH * 8 if s.L - 1 > A else 0
+    scores, n = 0, WR
+    for _ in range(s.L):
+        scores += n * HW * 4
+        n //= P_
+    shm = max(staged, sums) + scores
+    return None if shm > 160 * 1024 else (LR, HW, RG, WR, nt, shm)
+
+
+LEAF_EXTRA = [
+    ("deep", workloads.Config("deep", 1, 4096 * 3, 1, 1, 128, 4, 7, 4, "bf16", 1)),
+    ("deep_f32", workloads.Config("deep_f32", 1, 1024 * 2, 1, 1, 128, 4, 6, 4, "fp32", 1)),
+    ("p3_l6", workloads.Config("p3_l6", 2, 243 * 5, 2, 1, 64, 3, 6, 4, "bf16", 1)),
+    ("p2_l8", workloads.Config("p2_l8", 1, 128 * 3, 3, 1, 64, 2, 8, 4, "bf16", 1)),
+    ("short", workloads.Config("short", 1, 20, 5, 5, 128, 4, 2, 1, "bf16", 1)),
+]
+
+
+@pytest.mark.parametrize("name,c", [(n, c) for n, c, f in CASES if not f & 4 or c.flags & 4] + LEAF_EXTRA,
+                         ids=lambda x: x if isinstance(x, str) else "")
+def test_pool_leaf_index_math(name, c):
+    s = Shape(c)
+    if s.p not in (2, 3, 4):
+        pytest.skip("the walk kernel's shapes are checked above")
+    A, BR = {4: (2, 8), 3: (2, 9), 2: (3, 8)}[s.p]
+    got = _leaf_launch(s, A, BR)
+    if got is None and s.p == 4 and s.L >= 6:
+        A, BR = 3, 8
+        got = _leaf_launch(s, A, BR)
+    if got is None:
+        pytest.skip("too deep for a workgroup: the walk kernel's shapes are checked above")
+    LR, HW, RG, WR, nt, shm = got
+    CPR = 1 << s.cs
+    nslots = s.Hq + 2 * s.Hkv
+    assert nt == RG * HW * CPR <= 1024 and shm <= 160 * 1024
+    assert LR % BR == 0 and BR % s.p == 0
+    assert WR % s.P == 0 or s.P == 1, "a pooling window would straddle two workgroups"
+    nrow = -(-s.N // WR)
+    nchunk = -(-nslots // HW)
+    lin = np.arange(min(nrow * nchunk, 1 << 16))
+    once("leaf workgroups", (lin // nchunk) * nchunk + lin % nchunk, lin.size)
+    # thread (rg, hs, cc): rows w0 + rg LR + b0 + r; rows at or past N are neither read nor written
+    rows = (np.arange(nrow)[:, None] * WR + np.arange(WR)[None, :]).ravel()
+    once("leaf base rows", rows[rows < s.N], s.N)
+    # staged LDS row (hs RG + rg) BR + r, chunk cc; one norm thread per staged row
+    e = np.arange(HW * RG * BR)
+    hs, q = e // (RG * BR), e % (RG * BR)
+    g, r = q // BR, q % BR
+    once("leaf staged rows", (hs * RG + g) * BR + r, HW * RG * BR)
+    score_at = np.concatenate([hs * WR + g * LR + b0 + r for b0 in range(0, LR, BR)])
+    once("leaf level-0 scores", score_at, HW * WR)
+    base, nw, span = 0, WR, 1
+    for l in range(1, s.L):
+        n, span = nw // s.p, span * s.p
+        assert n * s.p == nw, "windows of a workgroup nest"
+        # children of window i of slot hs: hs nw + i p + r; the window itself at base + HW nw + hs n + i
+        child = (np.arange(HW)[:, None, None] * nw + np.arange(n)[None, :, None] * s.p + np.arange(s.p)).ravel()
+        once(f"leaf level-{l} children", child, HW * nw)
+        base += HW * nw
+        assert (base + HW * n) * 4 + (shm - sum(HW * (WR // s.p ** x) * 4 for x in range(s.L))) <= shm
+        # rows of level l: the thread's own windows (l <= A) or one window per row group
+        if l > A:
+            assert n <= RG, "a row group per window"
+            kids = (np.arange(n)[:, None] * s.p + np.arange(s.p)).ravel()
+            assert kids.max() < (RG if l == A + 1 else nw)
+        w = (np.arange(nrow)[:, None] * (WR // span) + np.arange(n)[None, :]).ravel()
+        valid = w * span < s.N
+        once(f"leaf level-{l} windows", w[valid], s.nrow[l])
+        inside(f"leaf level-{l} score", s.off[l] + w[valid], s.off[l] + w[valid] + 1, s.off[l + 1])
+        nw = n
