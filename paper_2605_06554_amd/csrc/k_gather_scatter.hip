@@ -746,6 +746,125 @@ __global__ void __launch_bounds__(256) scatter_bwd_kernel(ScatterBwdArgs a) {
   }
 }
 
+// ---------------------------------------------------------------- scatter_bwd, p = 2, 3, 4
+// Row groups (the walk above, spread out). A thread owns one 16-byte chunk of LR = p^A consecutive
+// shifted positions (a leaf) of one head: it copies its level-0 rows and closes the windows of
+// levels 1 .. A. A workgroup holds RG leaves of each of its HW heads, RG LR a multiple of p^(L-1);
+// the sums of the higher levels are formed level by level through LDS, each window adding its p
+// children in order, so every fp32 sum is the one a walk over the positions gives.
+//
+// Bound: HBM on long sequences; on short ones the latency of one workgroup's chain, which a walk
+// over 64 or more positions in steps of 8 made the whole time (see the launch).
+struct LeafBwdArgs {
+  const void* dout;  // [B, N, Hq, D]
+  const int32_t* slot;
+  void* dos;  // [B, Hq, S, D]
+  int64_t Ptot;
+  int32_t N, S, Hq, D, hw_shift, RG, nchunk;
+  int32_t cpr_shift, sub;  // chunks per thread row 1 << cpr_shift; a head is 1 << sub such slots
+  int32_t Hs, Gq;
+  int32_t off[8];
+  int32_t nrows[8];  // N / p^l
+};
+
+template <typename T, int P, int A, int L>
+__global__ void __launch_bounds__(1024) scatter_bwd_leaf_kernel(LeafBwdArgs a) {
+  constexpr int CH = 16 / sizeof(T);
+  constexpr int LR = ipow(P, A);
+  constexpr int LT = L - 1 < A ? L - 1 : A;  // levels closed by the thread
+  extern __shared__ __align__(16) float red[];
+  const int NT = blockDim.x, tid = threadIdx.x;
+  const int c0 = tid & ((1 << a.cpr_shift) - 1), grp = tid >> a.cpr_shift;
+  const int hs = grp & ((1 << a.hw_shift) - 1), rg = grp >> a.hw_shift;
+  const uint32_t rblk = blockIdx.x / (uint32_t)a.nchunk;  // position range; the slot chunk runs fastest
+  const int gs = ((int)(blockIdx.x - rblk * a.nchunk) << a.hw_shift) + hs;
+  const int hq = gs >> a.sub, cc = ((gs & ((1 << a.sub) - 1)) << a.cpr_shift) + c0;
+  const bool active = hq < a.Hq;
+  const int64_t b = blockIdx.y;
+  const int32_t w0 = (int32_t)rblk * a.RG * LR, u0 = w0 + rg * LR;
+  const int h = active ? hq : 0;
+  const int32_t* sl = a.slot + (b * a.Hs + h / a.Gq) * a.Ptot;
+  T* dos = reinterpret_cast<T*>(a.dos) + (b * a.Hq + h) * a.S * a.D + cc * CH;
+  const T* src = reinterpret_cast<const T*>(a.dout) + (b * a.N * a.Hq + h) * (int64_t)a.D + cc * CH;
+  const int64_t sstride = (int64_t)a.Hq * a.D;
+  // slot of the entry (l, w - 1) of window w, or -1
+  auto window_slot = [&](int l, int32_t w) __attribute__((always_inline)) -> int32_t {
+    return active && w >= 1 && w <= a.nrows[l] ? sl[a.off[l] + w - 1] : -1;
+  };
+  u32x4 v[LR];
+  int32_t m0[LR];
+#pragma unroll
+  for (int r = 0; r < LR; ++r) {
+    const int32_t u = u0 + r;
+    const bool valid = active && u >= 1 && u <= a.N;
+    v[r] = valid ? load16_nt(src + (int64_t)(u - 1) * sstride) : u32x4{0, 0, 0, 0};  // dout: read once
+    m0[r] = valid ? sl[u - 1] : -1;
+  }
+  int32_t ms[LT > 0 ? LT + 1 : 1][LR / P];
+  if constexpr (LT > 0) {
+#pragma unroll
+    for (int l = 1; l <= LT; ++l)
+#pragma unroll
+      for (int i = 0; i < LR / ipow(P, l); ++i) ms[l][i] = window_slot(l, u0 / ipow(P, l) + i);
+  }
+  float acc[A + 1][CH];
+#pragma unroll
+  for (int l = 0; l <= A; ++l)
+#pragma unroll
+    for (int e = 0; e < CH; ++e) acc[l][e] = 0.0f;
+#pragma unroll
+  for (int r = 0; r < LR; ++r) {
+    // level 0: entry u - 1 takes dout[u - 1] unchanged
+    if ((uint32_t)m0[r] < (uint32_t)a.S) store16_nt(dos + (int64_t)m0[r] * a.D, v[r]);
+    if constexpr (L > 1) {
+      add_chunk<T>(acc[1], v[r]);
+#pragma unroll
+      for (int l = 1; l <= LT; ++l) {
+        if ((r + 1) % ipow(P, l) != 0) break;
+        const int32_t m = ms[l][(r + 1) / ipow(P, l) - 1];
+        if ((uint32_t)m < (uint32_t)a.S) store_chunk<T>(dos + (int64_t)m * a.D, acc[l]);
+        if (l < A) {
+#pragma unroll
+          for (int e = 0; e < CH; ++e) acc[l + 1 <= A ? l + 1 : l][e] += acc[l][e];
+        }
+        if (l < A) {
+#pragma unroll
+          for (int e = 0; e < CH; ++e) acc[l][e] = 0.0f;
+        }
+      }
+    }
+  }
+  if constexpr (L - 1 > A) {
+#pragma unroll
+    for (int e = 0; e < CH; ++e) red[e * NT + tid] = acc[A][e];
+    int n = a.RG, span = LR;
+#pragma unroll
+    for (int l = A + 1; l < L; ++l) {
+      n /= P;
+      span *= P;
+      const int i = rg;  // window of the workgroup; its children sit at row groups i P .. i P + P - 1
+      const bool mine = i < n;
+      const int32_t m = mine ? window_slot(l, w0 / span + i) : -1;
+      __syncthreads();
+      float sum[CH];
+      if (mine) {
+#pragma unroll
+        for (int e = 0; e < CH; ++e) sum[e] = 0.0f;
+#pragma unroll
+        for (int r = 0; r < P; ++r)
+#pragma unroll
+          for (int e = 0; e < CH; ++e) sum[e] += red[e * NT + ((((i * P + r) << a.hw_shift) + hs) << a.cpr_shift) + c0];
+        if ((uint32_t)m < (uint32_t)a.S) store_chunk<T>(dos + (int64_t)m * a.D, sum);
+      }
+      __syncthreads();
+      if (mine) {
+#pragma unroll
+        for (int e = 0; e < CH; ++e) red[e * NT + tid] = sum[e];
+      }
+    }
+  }
+}
+
 // ---------------------------------------------------------------- host launchers
 
 static int cpr_shift_of(int D, int esize) {
@@ -879,9 +998,67 @@ static void run_grid(const RunArgs& a, int B, dim3* grid, dim3* block) {
   *block = dim3((unsigned)bs);
 }
 
+// Launches the leaf kernel; false if a workgroup cannot hold p^(L-1) positions.
+template <typename T, int P, int A, int L>
+static bool launch_scatter_bwd_leaf(const LhShape& s, const void* dout, const int32_t* slot, void* dos,
+                                    hipStream_t st) {
+  constexpr int LR = ipow(P, A);
+  const int64_t rg_min = s.P > LR ? s.P / LR : 1;
+  LeafBwdArgs a = {};
+  // columns are independent: where p^(L-1) positions of a whole head take more than 1024 threads, a
+  // slot is a half, a quarter, ... of a head, of 64 bytes or more
+  a.cpr_shift = cpr_shift_of(s.D, (int)sizeof(T));
+  while (a.cpr_shift > 2 && rg_min << a.cpr_shift > 1024) --a.cpr_shift, ++a.sub;
+  if (rg_min << a.cpr_shift > 1024) return false;
+  const int CPR = 1 << a.cpr_shift, nslots = s.Hq << a.sub;
+  a.dout = dout;
+  a.slot = slot;
+  a.dos = dos;
+  a.Ptot = s.Ptot;
+  a.N = (int32_t)s.N;
+  a.S = (int32_t)s.S;
+  a.Hq = s.Hq;
+  a.Hs = s.Hs;
+  a.Gq = s.Gq;
+  a.D = s.D;
+  // slots per workgroup: the largest power of two that fits 256 threads and leaves at most an
+  // eighth of the slots empty
+  for (int t = 1; t <= 4; ++t) {
+    const int hw = 1 << t, padded = (nslots + hw - 1) / hw * hw;
+    if (rg_min * CPR * hw <= 256 && padded * 8 <= nslots * 9) a.hw_shift = t;
+  }
+  const int64_t unit = rg_min * CPR << a.hw_shift;
+  a.RG = (int32_t)(rg_min * (unit >= 256 ? 1 : 256 / unit));
+  a.nchunk = (nslots + (1 << a.hw_shift) - 1) >> a.hw_shift;
+  for (int l = 0; l < s.L; ++l) {
+    a.off[l] = (int32_t)s.off[l];
+    a.nrows[l] = (int32_t)(s.N / s.pw[l]);
+  }
+  const int nt = (a.RG * CPR) << a.hw_shift;
+  const int64_t W = (int64_t)a.RG * LR, U = s.N + s.P;
+  const size_t shm = s.L - 1 > A ? (size_t)nt * (16 / sizeof(T)) * sizeof(float) : 0;
+  const dim3 grid((unsigned)((U + W - 1) / W * a.nchunk), (unsigned)s.B);
+  hipLaunchKernelGGL((scatter_bwd_leaf_kernel<T, P, A, L>), grid, dim3((unsigned)nt), shm, st, a);
+  return true;
+}
+
+// Leaves for p = 2, 3, 4 at every size measured; the walk for other p and for pyramids too deep for a
+// workgroup. Walk -> leaves, us: N = 8192, 8 heads, p = 4, L = 3 21.7 -> 12.0; 24,576, 12 heads of
+// 64, p = 2, L = 6 31.9 -> 13.4; 16,384, 1 head, p = 4, L = 6 227 -> 12.9; 524,288, 8 heads, L = 3, k
+// = 16,384 276 -> 246; 262,144, 32 heads, L = 5 511 -> 497 (5.2 TB/s).
+template <typename T, int L>
+static bool launch_scatter_bwd_leaves(const LhShape& s, const void* dout, const int32_t* slot, void* dos,
+                                      hipStream_t st) {
+  if (s.p == 4) return launch_scatter_bwd_leaf<T, 4, 2, L>(s, dout, slot, dos, st);
+  if (s.p == 3) return launch_scatter_bwd_leaf<T, 3, 2, L>(s, dout, slot, dos, st);
+  if (s.p == 2) return launch_scatter_bwd_leaf<T, 2, 3, L>(s, dout, slot, dos, st);
+  return false;
+}
+
 template <typename T, int L>
 static hipError_t launch_scatter_bwd_T(const LhShape& s, const void* dout, const int32_t* slot,
                                        void* dos, hipStream_t st) {
+  if (launch_scatter_bwd_leaves<T, L>(s, dout, slot, dos, st)) return hipGetLastError();
   ScatterBwdArgs a = {};
   a.dout = dout;
   a.slot = slot;

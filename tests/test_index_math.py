@@ -572,3 +572,45 @@ def test_pool_leaf_index_math(name, c):
         once(f"leaf level-{l} windows", w[valid], s.nrow[l])
         inside(f"leaf level-{l} score", s.off[l] + w[valid], s.off[l] + w[valid] + 1, s.off[l + 1])
         nw = n
+
+
+# ---------------------------------------------------------------- scatter_bwd_leaf_kernel
+
+@pytest.mark.parametrize("name,c", [(n, c) for n, c, f in CASES if not f & 4 or c.flags & 4] + LEAF_EXTRA,
+                         ids=lambda x: x if isinstance(x, str) else "")
+def test_scatter_bwd_leaf_index_math(name, c):
+    s = Shape(c)
+    if s.p not in (2, 3, 4):
+        pytest.skip("the walk kernel's shapes are checked above")
+    A = {4: 2, 3: 2, 2: 3}[s.p]
+    LR = s.p ** A
+    rg_min, cpr, sub = max(s.P // LR, 1), s.cs, 0
+    while cpr > 2 and rg_min << cpr > 1024:
+        cpr, sub = cpr - 1, sub + 1
+    if rg_min << cpr > 1024:
+        pytest.skip("too deep for a workgroup: the walk kernel's shapes are checked above")
+    nslots, CPR = s.Hq << sub, 1 << cpr
+    sh = max([0] + [t for t in range(1, 5) if rg_min * CPR << t <= 256
+                    and -(-nslots // (1 << t)) * (1 << t) * 8 <= nslots * 9])
+    unit = rg_min * CPR << sh
+    RG = rg_min * (1 if unit >= 256 else 256 // unit)
+    nt, W, U = RG * CPR << sh, RG * LR, s.N + s.P
+    assert nt <= 1024 and W % s.P == 0
+    nchunk = -(-nslots // (1 << sh))
+    gs = np.arange(nchunk << sh)
+    head, cc0 = gs >> sub, (gs & ((1 << sub) - 1)) << cpr
+    ok = head < s.Hq
+    once("scatter_bwd chunks", ((head[ok] << s.cs) + cc0[ok])[:, None] + np.arange(CPR), s.Hq << s.cs)
+    nblk = -(-U // W)
+    u = (np.arange(nblk)[:, None] * W + np.arange(W)).ravel()
+    valid = (u >= 1) & (u <= s.N)
+    once("scatter_bwd level-0 rows", u[valid] - 1, s.N)
+    span, n = 1, W
+    for l in range(1, s.L):
+        span, n = span * s.p, n // s.p
+        w = (np.arange(nblk)[:, None] * (W // span) + np.arange(n)).ravel()  # windows of every workgroup
+        entry = w[(w >= 1) & (w <= s.nrow[l])] - 1
+        once(f"scatter_bwd level-{l} entries", entry, s.nrow[l])
+        if l > A:
+            kids = (np.arange(n)[:, None] * s.p + np.arange(s.p)).ravel()
+            once(f"scatter_bwd level-{l} children", kids, RG // s.p ** (l - 1 - A))
