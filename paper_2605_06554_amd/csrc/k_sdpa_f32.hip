@@ -1,27 +1,34 @@
-// k_sdpa_f32.hip -- fp32 causal SDPA on the gathered sub-sequence with fp32 MFMA
+// k_sdpa_f32.hip -- fp32 causal SDPA on the gathered sub-sequence with bf16 MFMA on split operands
 // (Sec. 3.5, Eq. attn-sub with Eq. sdpa): forward, and the deterministic backward (dK/dV and dQ
 // workgroups in one launch), per (b, hq) over [S, D] rows.
 //
-// Bound and split. v_mfma_f32_32x32x2_f32 takes 64 clocks for 4096 operations, so a 32 x 32 tile
-// of one product at D = 128 is 4096 clocks of one SIMD, against a few hundred for its softmax
-// and about 2000 for the latency of its loads: the kernels are bound by the matrix unit as soon
-// as every SIMD has a wave. fp32 problems are small (a few thousand rows, a few heads), so the
-// split is for many waves: a workgroup owns 32 rows, and its NF waves share out the 32-row tiles
-// that those rows meet (wave f takes tiles f, f + NF, ...). Each wave streams its tiles into LDS
-// buffers of its own, without a barrier in the loop: the two operand tiles are used in different
-// phases, so each is reloaded as soon as its last phase is done and lands under the next phase.
-// The waves' partial results are summed in LDS at the end, in wave order (deterministic).
-// Measured against a thread per row (64-row workgroups, fp32 FMAs from LDS, registers spilled):
-// a layer's forward and backward at S = 2257, 8 query heads, D = 128 took 71.7 ms and takes
-// 0.64 ms; at S = 832, 2 heads, D = 64, 2.85 ms and 0.15 ms. The error against 64 bits fell too
-// (1.2e-6 to 7e-7, 7e-7 to 4e-7 of the 2-norm, dK at worst).
+// Arithmetic. An fp32 value is the exact sum of three bf16 values (8 + 8 + 8 bits). A product of two
+// is formed from six of the nine products of their parts, exact each, summed in the MFMA's fp32
+// accumulator; what is left out is below 2^-23 of a product and of either sign, less than the fp32
+// accumulation itself rounds off. Measured against 64 bits (2-norm, S = 2257, 8 heads, D = 128): o
+// 2.9e-7, dQ 4.7e-7, dK 6.3e-7, dV 5.9e-7; with fp32 MFMA (v_mfma_f32_32x32x2) 3.6e-7, 5.5e-7,
+// 7.5e-7, 7.0e-7; with fp32 FMAs, a thread per row, dK 1.2e-6. 16 columns of a 32 x 32 tile take 6
+// MFMAs of 32 clocks; the fp32 MFMA takes 8 of 64.
+//
+// Bound and split. A wave splits the streamed operand as it reads it (44 VALU instructions of 4
+// clocks per 6 MFMAs), so the vector and the matrix units are about equally busy, and on few or short
+// heads the time is that of a workgroup's chain of tiles. fp32 problems are small (a few thousand
+// rows, a few heads), so the split of the work is for many waves: a workgroup owns 32 rows, and its
+// NF waves share out the 32-row tiles that those rows meet (wave f takes tiles f, f + NF, ...). Each
+// wave streams its tiles into LDS buffers of its own, without a barrier in the loop: the two operand
+// tiles are used in different phases, so each is reloaded as soon as its last phase is done and lands
+// under the next phase. The waves' partial results are summed in LDS at the end, in wave order
+// (deterministic).
+// Measured, forward / backward: S = 2257, 8 heads, D = 128: a thread per row 8950 / 62,900 us; fp32
+// MFMA in this split 149 / 410; this 109 / 316. S = 832, 2 heads, D = 64: 945 / 1780; 24 / 43; 18 / 39.
+// S = 6000, 8 heads, D = 128: fp32 MFMA 744 / 2266, this 543 / 1739.
 //
 // Layout facts (lane l of a wave, h = l / 32):
-//   MFMA 32x32x2: A[m = l % 32][k = h], B[k = h][n = l % 32],
-//                 C[m = 8 (i / 4) + 4 h + i % 4][n = l % 32], i = 0..15.
-//   A product over D takes its k in the order 8 kk + 4 h + j, so a lane's operands of four MFMAs
-//   are one 16-byte read. A product over the 32 rows of a tile takes row 8 (i / 4) + 4 h + i % 4
-//   at step i, so accumulator element i is that step's operand as it is.
+//   MFMA 32x32x16: A[m = l % 32][k = 8 h + 0..7], B[k = 8 h + 0..7][n = l % 32],
+//                  C[m = 8 (i / 4) + 4 h + i % 4][n = l % 32], i = 0..15.
+//   A product over D takes columns 16 s + 4 h + 0..3 and 16 s + 8 + 4 h + 0..3 as a lane's 8 (two
+//   16-byte reads). A product over the 32 rows of a tile takes rows 8 (i / 4) + 4 h + i % 4 for i =
+//   8 u .. 8 u + 7, so the accumulator elements of those i, split, are that step's operand.
 //
 // LDS tiles: 32 rows of D floats, chunk c (16 bytes) of row r at position c ^ (r mod chunks), so
 // that the lanes reading one chunk of consecutive rows hit different banks.
@@ -33,8 +40,50 @@ namespace lh {
 
 constexpr float kLog2eF = 1.4426950408889634f;
 
-__device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+__device__ __forceinline__ f32x16 mfma_b16(bf16x8 a, bf16x8 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
+// 8 fp32 values as three bf16 vectors whose sum they are, exactly: h is the value cut to its top 16
+// bits (8 significant ones; cut, not rounded, so that no finite value becomes infinite), m the rest
+// rounded to 8 bits, l what is left, which has 8 bits or fewer.
+struct Split8 {
+  bf16x8 h, m, l;
+};
+typedef __attribute__((__vector_size__(8 * sizeof(float)))) float f32x8;
+typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4s;
+__device__ __forceinline__ Split8 split8(const float* x) {
+  Split8 r;
+  u32x4s hp;
+  f32x8 d, e;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t a = __float_as_uint(x[2 * i]), b = __float_as_uint(x[2 * i + 1]);
+    hp[i] = __builtin_amdgcn_perm(b, a, 0x07060302u);  // the upper halves of a and b
+    d[2 * i] = x[2 * i] - __uint_as_float(a & 0xffff0000u);
+    d[2 * i + 1] = x[2 * i + 1] - __uint_as_float(b & 0xffff0000u);
+  }
+  r.h = __builtin_bit_cast(bf16x8, hp);
+  r.m = __builtin_convertvector(d, bf16x8);
+  const u32x4s mp = __builtin_bit_cast(u32x4s, r.m);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    e[2 * i] = d[2 * i] - __uint_as_float(mp[i] << 16);
+    e[2 * i + 1] = d[2 * i + 1] - __uint_as_float(mp[i] & 0xffff0000u);
+  }
+  r.l = __builtin_convertvector(e, bf16x8);
+  return r;
+}
+
+// acc += a b: the six products of the parts down to 2^-16 of the whole, smallest first. What is
+// left out (m l, l m, l l) is below 2^-23 of a product and of either sign.
+__device__ __forceinline__ f32x16 mfma_split(const Split8& a, const Split8& b, f32x16 acc) {
+  acc = mfma_b16(a.m, b.m, acc);
+  acc = mfma_b16(a.l, b.h, acc);
+  acc = mfma_b16(a.h, b.l, acc);
+  acc = mfma_b16(a.m, b.h, acc);
+  acc = mfma_b16(a.h, b.m, acc);
+  return mfma_b16(a.h, b.h, acc);
 }
 
 // Waits until at most N of this wave's vector-memory loads are outstanding and its LDS reads
@@ -90,68 +139,84 @@ struct Tile32 {
   }
 };
 
-// Row l % 32 of 32 rows from r0 in registers: element 4 kk + j is column 8 kk + 4 h + j.
+// A lane's row in registers, split: operand s holds columns 16 s + 4 h + 0..3 and 16 s + 8 + 4 h + 0..3.
 template <int D>
-__device__ __forceinline__ void load_row_regs(const float* src, int row, int h, float* out) {
+__device__ __forceinline__ void load_row_regs(const float* src, int row, int h, Split8* out) {
 #pragma unroll
-  for (int kk = 0; kk < D / 8; ++kk) {
-    const float4 x = *reinterpret_cast<const float4*>(src + (int64_t)row * D + 8 * kk + 4 * h);
-    out[4 * kk] = x.x, out[4 * kk + 1] = x.y, out[4 * kk + 2] = x.z, out[4 * kk + 3] = x.w;
+  for (int s = 0; s < D / 16; ++s) {
+    const float4 x = *reinterpret_cast<const float4*>(src + (int64_t)row * D + 16 * s + 4 * h);
+    const float4 y = *reinterpret_cast<const float4*>(src + (int64_t)row * D + 16 * s + 8 + 4 * h);
+    const float f[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+    out[s] = split8(f);
   }
 }
 
-// acc += tile (rows = m) x regs^T (rows = n) over D. Two operand reads (8 MFMAs, 512 clocks) run
-// ahead of the MFMAs that use them: alone on its SIMD, a wave otherwise waits out each read.
+// Order of a step's instructions. A wave that has its SIMD to itself (D = 128, up to 512 registers)
+// runs a sixth of the next operands' split between any two MFMAs: S = 2257, 8 heads 103 / 302 us
+// against 106 / 321 in the compiler's order. With two waves per SIMD (D = 64) the other wave fills
+// the gaps, and each step is closed off so that fewer operands are live: 55 / 162 us against 53 / 175.
 template <int D>
-__device__ __forceinline__ f32x16 rows_product(const Tile32<D>& tl, const float* t, const float* regs, f32x16 acc) {
-  float4 cur[2] = {tl.row(t, 0), tl.row(t, 1)};
+__device__ __forceinline__ void mix_split() {
+  if constexpr (D == 128) {
 #pragma unroll
-  for (int kk = 0; kk < D / 8; kk += 2) {
-    float4 nxt[2] = {cur[0], cur[1]};
-    if (kk + 2 < D / 8) nxt[0] = tl.row(t, kk + 2), nxt[1] = tl.row(t, kk + 3);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      acc = mfma_f32(cur[u].x, regs[4 * (kk + u)], acc);
-      acc = mfma_f32(cur[u].y, regs[4 * (kk + u) + 1], acc);
-      acc = mfma_f32(cur[u].z, regs[4 * (kk + u) + 2], acc);
-      acc = mfma_f32(cur[u].w, regs[4 * (kk + u) + 3], acc);
+    for (int i = 0; i < 6; ++i) {  // groups: MFMA (0x008), DS reads (0x100), VALU (0x002)
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+      __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);
     }
+  } else {
     __builtin_amdgcn_sched_barrier(0);
-    cur[0] = nxt[0], cur[1] = nxt[1];
+  }
+}
+
+// acc += tile (rows = m) x regs^T (rows = n) over D. The reads and the split of the next 16 columns
+// run under the MFMAs of the current ones.
+template <int D>
+__device__ __forceinline__ f32x16 rows_product(const Tile32<D>& tl, const float* t, const Split8* regs, f32x16 acc) {
+  auto get = [&](int s) __attribute__((always_inline)) {
+    const float4 x = tl.row(t, 2 * s), y = tl.row(t, 2 * s + 1);
+    const float f[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+    return split8(f);
+  };
+  Split8 cur = get(0);
+#pragma unroll
+  for (int s = 0; s < D / 16; ++s) {
+    Split8 nxt = cur;
+    if (s + 1 < D / 16) nxt = get(s + 1);
+    acc = mfma_split(cur, regs[s], acc);
+    mix_split<D>();
+    cur = nxt;
   }
   return acc;
 }
 
 // acc[d] += product over the tile's 32 rows of its columns and x (element i: row 8 (i / 4) + 4 h +
-// i % 4). XA: x is the row operand (rows of the result come from x), else the column operand. The
-// reads of the next four rows run ahead of the MFMAs.
+// i % 4). XA: x is the row operand (rows of the result come from x), else the column operand.
 template <int D, bool XA>
 __device__ __forceinline__ void cols_product(const Tile32<D>& tl, const float* t, f32x16 x, f32x16* acc) {
-  constexpr int ND = D / 32, G = 128 / D;  // G steps of ND columns: 4 reads in flight
-  float cur[G][ND];
+  constexpr int ND = D / 32;
+  auto get = [&](int u, int d) __attribute__((always_inline)) {
+    float f[8];
 #pragma unroll
-  for (int g = 0; g < G; ++g)
+    for (int j = 0; j < 8; ++j) f[j] = tl.at(t, 8 * u + j, d);
+    return split8(f);
+  };
+  Split8 cur = get(0, 0);
 #pragma unroll
-    for (int d = 0; d < ND; ++d) cur[g][d] = tl.at(t, g, d);
+  for (int u = 0; u < 2; ++u) {
+    float f[8];
 #pragma unroll
-  for (int i = 0; i < 16; i += G) {
-    float nxt[G][ND];
+    for (int j = 0; j < 8; ++j) f[j] = x[8 * u + j];
+    const Split8 xs = split8(f);
 #pragma unroll
-    for (int g = 0; g < G; ++g)
-#pragma unroll
-      for (int d = 0; d < ND; ++d) nxt[g][d] = i + G < 16 ? tl.at(t, i + G + g, d) : 0.0f;
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-#pragma unroll
-      for (int d = 0; d < ND; ++d)
-        acc[d] = XA ? mfma_f32(x[i + g], cur[g][d], acc[d]) : mfma_f32(cur[g][d], x[i + g], acc[d]);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-#pragma unroll
-      for (int d = 0; d < ND; ++d) cur[g][d] = nxt[g][d];
+    for (int d = 0; d < ND; ++d) {
+      Split8 nxt = cur;
+      if (d + 1 < ND) nxt = get(u, d + 1);
+      else if (u == 0) nxt = get(1, 0);
+      acc[d] = XA ? mfma_split(xs, cur, acc[d]) : mfma_split(cur, xs, acc[d]);
+      mix_split<D>();
+      cur = nxt;
+    }
   }
 }
 
@@ -199,7 +264,7 @@ sdpa_fwd_f32(const float* __restrict__ Q, const float* __restrict__ K, const flo
   float* kt = Kt[f];
   float* vt = Vt[f];
   const T tl(lane);
-  float q[D / 2];
+  Split8 q[D / 16];
   load_row_regs<D>(Q + bh * S * D, myq < S ? myq : S - 1, h, q);
   f32x16 o[D / 32];
 #pragma unroll
@@ -306,7 +371,7 @@ __device__ __forceinline__ void dq_block(const BwdF32& a, int64_t lin, float (*A
   float* vt = Bt[f];
   const T tl(lane);
   const int row = myq < S ? myq : S - 1;
-  float q[D / 2], go[D / 2];
+  Split8 q[D / 16], go[D / 16];
   load_row_regs<D>(a.q + bh * S * D, row, h, q);
   load_row_regs<D>(a.go + bh * S * D, row, h, go);
   const float lse = a.lse[bh * S + row], ndl = -a.delta[bh * S + row];
@@ -374,7 +439,7 @@ __device__ __forceinline__ void dkdv_block(const BwdF32& a, int64_t lin, float (
   float* stat = st[f];  // lse of the tile's rows, then -Delta
   const T tl(lane);
   const int row = mykey < S ? mykey : S - 1;
-  float k[D / 2], v[D / 2];
+  Split8 k[D / 16], v[D / 16];
   load_row_regs<D>(a.k + bs * S * D, row, h, k);
   load_row_regs<D>(a.v + bs * S * D, row, h, v);
   f32x16 dk[D / 32], dv[D / 32];
