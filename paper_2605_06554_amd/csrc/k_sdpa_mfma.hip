@@ -435,12 +435,11 @@ sdpa_fwd_bf16(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const 
     const bf16_t* qr = IDX ? rs_row(qsrc, idxh[qrow]) : Qh + (int64_t)qrow * D;
     qreg[kk] = gld8(qr + 16 * kk + 8 * h);
   }
-  load_kv(0, 0);
+  if constexpr (F == 1) load_kv(0, 0);
   f32x16 oacc[D / 32];
 #pragma unroll
   for (int d = 0; d < D / 32; ++d) oacc[d] = f32x16{};
   float m_run = -INFINITY, l_run = 0.0f;
-  __shared__ float ms[F > 1 ? FW : 1][32], ls[F > 1 ? FW : 1][32];
 
   // S^T = K Q^T of this wave's keys of a tile, masked on the diagonal
   auto logits = [&](const bf16_t* Kt, int k0, f32x16* sacc) __attribute__((always_inline)) {
@@ -467,21 +466,149 @@ sdpa_fwd_bf16(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const 
     return fmaxf(mloc, __shfl_xor(mloc, 32, 64)) * sl2;
   };
   if constexpr (F > 1) {
-    // Every wave starts from the maximum of the row's first 64 keys, as F = 1 does: P is then
-    // rounded to bf16 at the same scale whatever the split (until a maximum grows by 2^8), and a
-    // wave whose own first keys are all masked for a row has a finite maximum.
-    sync_tiles<0>();  // tile 0 has landed
-    if (f < 2) {
-      float mloc = -INFINITY;
-      if (qw + 31 >= 32 * f) {
-        f32x16 sacc[NB];
-        logits(Ks0, 32 * f, sacc);
-        mloc = row_max(sacc);
+    // The running maximum of a row follows the maxima of its 64-key tiles, whichever waves hold
+    // them, so P is rounded to bf16 at the scale that F = 1 gives it (with a maximum of its own per
+    // wave, outputs moved by 1e-3 of their 2-norm where maxima grow by more than 2^8). A wave
+    // leaves its keys' row maxima of tile t in LDS before the barrier that opens step t + 1 and
+    // weighs the tile after it, so the exchange takes no barrier of its own: step t forms the
+    // logits of tile t and weighs tile t - 1, and V streams one tile behind K. Against a maximum of
+    // its own per wave and no such overlap: D = 128 0.92 to 1.00 of the time (3000 rows, 8 heads,
+    // F = 4: 38.5 -> 35.9 us), D = 64 1.00 to 1.04 (12,000, 8, F = 2: 230 -> 239).
+    static_assert(NB == 1, "one 32-key block of a tile per wave");
+    constexpr int FR = C::R;
+    __shared__ float mt[2][FW][32];  // row maxima of every wave's keys of a tile
+    __shared__ float ms[FW][32], ls[FW][32];
+    const int r = w % FR;
+    float m_row = -INFINITY;  // the row's running maximum after the last weighed tile
+    int32_t v_ids[LPW];  // ids of the tile that K was last loaded of; kv_ids: of the next
+    auto load_k = [&](int slot_, int r0) __attribute__((always_inline)) {
+      if constexpr (IDX) {
+        load_tile_idx<D, FK, FW>(slot_ ? Ks1 : Ks0, ksrc, kv_ids, w, lane);
+#pragma unroll
+        for (int j = 0; j < LPW; ++j) v_ids[j] = kv_ids[j];  // V of this tile is loaded next
+        tile_ids<D, FK, FW>(idxh, r0 + FK, S, w, lane, kv_ids);
+      } else {
+        load_tile<D, FK, FW>(slot_ ? Ks1 : Ks0, Kh, r0, S, w, lane);
       }
-      if (h == 0) ms[w][r32] = mloc;
-    }
+    };
+    // The row's maximum after each 64 keys of the tile in slot SL; returns the one for this wave's keys.
+    float mv[F];
+    auto get_max = [&](auto slotc) __attribute__((always_inline)) {
+#pragma unroll
+      for (int x = 0; x < F; ++x) mv[x] = mt[decltype(slotc)::value][x * FR + r][r32];
+    };
+    auto tile_max = [&]() __attribute__((always_inline)) {
+      float mine = m_row;
+#pragma unroll
+      for (int x = 0; x < F; x += 2) {
+        const float m = fmaxf(mv[x], mv[x + 1]);
+        if (m > m_row + kRescale) m_row = m;
+        if (f >= x) mine = m_row;
+      }
+      return mine;
+    };
+    auto rescale = [&](float m) __attribute__((always_inline)) {
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m);
+      l_run *= alpha;
+#pragma unroll
+      for (int d = 0; d < D / 32; ++d)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) oacc[d][i] *= alpha;
+      m_run = m;
+    };
+    // P of 16 of the 32 keys
+    auto soft = [&](const f32x16& s, int u) __attribute__((always_inline)) {
+      float p[8];
+#pragma unroll
+      for (int t = 0; t < 8; ++t) p[t] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[8 * u + t], sl2, -m_run));
+      l_run += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+      return cvt8(p);
+    };
+    auto pv = [&](const bf16_t* Vt, const bf16x8& p0, const bf16x8& p1) __attribute__((always_inline)) {
+#pragma unroll
+      for (int d = 0; d < D / 32; ++d) oacc[d] = mfma32(tr8(Vt, lo.trl[d], lo.trh[d]), p0, oacc[d]);
+#pragma unroll
+      for (int d = 0; d < D / 32; ++d)
+        oacc[d] = mfma32(tr8(Vt, 16 * RB + lo.trl[d], 16 * RB + lo.trh[d]), p1, oacc[d]);
+    };
+    f32x16 sp[1] = {f32x16{}};  // logits of the tile before
+    auto put_max = [&](auto slotc, float m) __attribute__((always_inline)) {
+      if (h == 0) mt[decltype(slotc)::value][w][r32] = m;
+    };
+    // waits for K of tile kt and V of tile kt - 1, whose other slots are free, and loads the next
+    auto turn = [&](auto slotc, int kt) __attribute__((always_inline)) {
+      constexpr int SL = decltype(slotc)::value;
+      sync_tiles<0>();
+      get_max(IC<SL ^ 1>{});
+      if constexpr (IDX) load_tile_idx<D, FK, FW>(SL ? Vs1 : Vs0, vsrc, v_ids, w, lane);
+      else load_tile<D, FK, FW>(SL ? Vs1 : Vs0, Vh, kt * FK, S, w, lane);
+      load_k(SL ^ 1, (kt + 1) * FK);
+    };
+    const int kw = 32 * f;  // this wave's first key of a tile
+    load_k(0, 0);
+    turn(IC<0>{}, 0);
+    if (qw + 31 >= kw) logits(Ks0, kw, sp);
+    put_max(IC<0>{}, qw + 31 >= kw ? row_max(sp) : -INFINITY);
+    auto step = [&](auto slotc, int kt) __attribute__((always_inline)) {
+      constexpr int SL = decltype(slotc)::value;
+      turn(slotc, kt);
+      const int k0 = kt * FK + kw;
+      const bf16_t* const Kt = SL ? Ks1 : Ks0;
+      float mloc = -INFINITY;
+      f32x16 s = f32x16{};  // half of the logits while the maxima arrive
+#pragma unroll
+      for (int kk = 0; kk < D / 32; ++kk) s = mfma32(row8(Kt, lo.row[kk]), qreg[kk], s);
+      const float mine = tile_max();
+      if (qw + 31 >= k0 - FK) {  // else every key of its share was in the future of its rows
+        if (mine > m_run) rescale(mine);
+        __builtin_amdgcn_sched_barrier(0);
+        // the rest of them under the softmax of the last tile (in the compiler's order: with
+        // scheduling groups the kernel took 4 to 10% longer)
+#pragma unroll
+        for (int kk = D / 32; kk < D / 16; ++kk) s = mfma32(row8(Kt, lo.row[kk]), qreg[kk], s);
+        const bf16x8 p0 = soft(sp[0], 0), p1 = soft(sp[0], 1);
+        pv(SL ? Vs0 : Vs1, p0, p1);
+        if (k0 + 31 > qw) {
+#pragma unroll
+          for (int i = 0; i < 16; ++i)
+            if (k0 + 8 * (i >> 2) + 4 * h + (i & 3) > myq) s[i] = -INFINITY;
+        }
+        sp[0] = s;
+        mloc = row_max(sp);
+      }
+      put_max(slotc, mloc);
+    };
+    // the last tile: V of tile nkt - 1, in slot SL
+    auto last = [&](auto slotc) __attribute__((always_inline)) {
+      constexpr int SL = decltype(slotc)::value;
+      sync_tiles<0>();
+      get_max(slotc);
+      const float mine = tile_max();
+      if (qw + 31 >= (nkt - 1) * FK + kw) {
+        if (mine > m_run) rescale(mine);
+        const bf16x8 p0 = soft(sp[0], 0), p1 = soft(sp[0], 1);
+        pv(SL ? Vs1 : Vs0, p0, p1);
+      }
+    };
+    ring2_loop(1, nkt, step);
+    if (nkt & 1) last(IC<0>{});
+    else last(IC<1>{});
+    const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+    if (h == 0) ms[w][r32] = m_run, ls[w][r32] = l_tot;
     __syncthreads();
-    m_run = fmaxf(ms[w % C::R][r32], ms[C::R + w % C::R][r32]);
+    float l = 0.0f, wt[F];
+#pragma unroll
+    for (int x = 0; x < F; ++x) {
+      wt[x] = __builtin_amdgcn_exp2f(ms[x * FR + r][r32] - m_row);  // 0 for a wave without a key of the row
+      l += wt[x] * ls[x * FR + r][r32];
+    }
+    const float inv = 1.0f / l;
+    bf16_t* orow = O + (bh * S + myq) * D;
+    combine<D, F, FR>(Ring<0>{Ks0, Ks1, Vs0, Vs1}, oacc, wt, w, lane, [&](int d, int g, const float* v) {
+      if (myq < S) store_quad(orow + 32 * d + 8 * g + 4 * h, v, inv);
+    });
+    if (myq < S && f == 0 && h == 0) LSE[bh * S + myq] = (m_row + __log2f(l)) * kLn2;
+    return;
   }
 
   auto step = [&](auto slotc, int kt) {
@@ -546,27 +673,6 @@ sdpa_fwd_bf16(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const 
     if (t0 + 1 < nkt) step(IC<1>{}, t0 + 1);
   }
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
-  if constexpr (F > 1) {
-    sync_tiles<0>();  // the last (unused) tile has landed
-    if (h == 0) ms[w][r32] = m_run, ls[w][r32] = l_tot;
-    __syncthreads();
-    const int r = w % C::R;
-    float M = ms[r][r32], l = 0.0f, wt[F];
-#pragma unroll
-    for (int x = 1; x < F; ++x) M = fmaxf(M, ms[x * C::R + r][r32]);
-#pragma unroll
-    for (int x = 0; x < F; ++x) {
-      wt[x] = __builtin_amdgcn_exp2f(ms[x * C::R + r][r32] - M);  // 0 for a wave without a key of the row
-      l += wt[x] * ls[x * C::R + r][r32];
-    }
-    const float inv = 1.0f / l;
-    bf16_t* orow = O + (bh * S + myq) * D;
-    combine<D, F, C::R>(Ring<0>{Ks0, Ks1, Vs0, Vs1}, oacc, wt, w, lane, [&](int d, int g, const float* v) {
-      if (myq < S) store_quad(orow + 32 * d + 8 * g + 4 * h, v, inv);
-    });
-    if (myq < S && f == 0 && h == 0) LSE[bh * S + myq] = (M + __log2f(l)) * kLn2;
-    return;
-  }
   if (myq < S) {
     store_qrow<D>(O + (bh * S + myq) * D, oacc, 1.0f / l_tot, h);
     if (h == 0) LSE[bh * S + myq] = (m_run + __log2f(l_tot)) * kLn2;

@@ -119,3 +119,41 @@ def test_indexed_equals_gathered(S, Hq, Hkv, D):
     for name, a, b in zip(("os", "lse", "dqs", "dks", "dvs"), *got):
         assert torch.equal(a.view(torch.int16 if a.dtype == torch.bfloat16 else torch.int32),
                            b.view(torch.int16 if b.dtype == torch.bfloat16 else torch.int32)), name
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("data", ["growing", "spikes", "ramp"])
+def test_bf16_splits_round_alike(data, D, rng):
+    """A row's softmax weights are rounded to bf16 at one scale, whichever split of its keys runs: a
+    head alone (4 waves a row block), among 100 (2 waves) and among 160 (one) gives the same rows
+    but for the order of fp32 sums. The maxima of the rows' logits grow by far more than the 2^8 at
+    which the accumulators are rescaled. Bound: sums of up to 700 products differ by 2^-20 of the sum
+    of their sizes, so one element in 2^12 rounds to the other neighbour, 2^-8 away: 2^-14 of the
+    2-norm; four times that for sums that cancel."""
+    S = 700
+    print(f"[sdpa edges] splits round alike S={S} D={D} {data}", flush=True)
+    q, k, v = (rng.standard_normal((S, D)) for _ in range(3))
+    if data == "growing":
+        k *= np.linspace(0.5, 16, S)[:, None]
+    elif data == "spikes":
+        k[rng.permutation(S)[:S // 20]] *= 8.0
+        k[:S // 2] *= 0.25
+    else:  # every row's logits climb along the sequence, and fall again for the other half of the rows
+        u = rng.standard_normal(D) / np.sqrt(D)
+        k += np.linspace(0, 24, S)[:, None] * u * np.sqrt(D)
+        q += np.where(rng.random(S) < 0.5, 1.0, -1.0)[:, None] * u * np.sqrt(D)
+    got = []
+    for H in (1, 100, 160):
+        pr = lh.problem(1, S, H, H, D, 2, 1, 0, torch.bfloat16)
+        x = [torch.from_numpy(t).to(torch.bfloat16).to(DEV).expand(1, H, S, D).contiguous() for t in (q, k, v)]
+        o = torch.full_like(x[0], float("nan"))
+        lse = torch.full((1, H, S), float("nan"), device=DEV)
+        lh.lh_sdpa_fwd(pr, *x, o, lse)
+        torch.cuda.synchronize()
+        assert bool((o == o[:, :1]).all()) and bool((lse == lse[:, :1]).all()), "equal heads differ"
+        got.append((o[0, 0].double(), lse[0, 0].double()))
+    for o, lse in got[:2]:
+        d = ((o - got[2][0]).norm() / got[2][0].norm()).item()
+        print(f"  2-norm of the difference {d:.2e}, lse {(lse - got[2][1]).abs().max().item():.2e}", flush=True)
+        assert d <= 2.0 ** -12
+        assert (lse - got[2][1]).abs().max().item() <= 1e-5 * max(1.0, got[2][1].abs().max().item())
