@@ -2,13 +2,15 @@
 // (Sec. 3.5, Eq. attn-sub with Eq. sdpa): forward, and the deterministic backward (dK/dV and dQ
 // workgroups in one launch), per (b, hq) over [S, D] rows.
 //
-// Arithmetic. An fp32 value is the exact sum of three bf16 values (8 + 8 + 8 bits). A product of two
-// is formed from six of the nine products of their parts, exact each, summed in the MFMA's fp32
-// accumulator; what is left out is below 2^-23 of a product and of either sign, less than the fp32
-// accumulation itself rounds off. Measured against 64 bits (2-norm, S = 2257, 8 heads, D = 128): o
-// 2.9e-7, dQ 4.7e-7, dK 6.3e-7, dV 5.9e-7; with fp32 MFMA (v_mfma_f32_32x32x2) 3.6e-7, 5.5e-7,
-// 7.5e-7, 7.0e-7; with fp32 FMAs, a thread per row, dK 1.2e-6. 16 columns of a 32 x 32 tile take 6
-// MFMAs of 32 clocks; the fp32 MFMA takes 8 of 64.
+// Arithmetic. An fp32 value is split into three bf16 values (8 + 8 + 8 bits), whose sum it is
+// exactly where its low part is in bf16's normal range (2^-103 and up). A product is formed
+// from six of the nine products of parts, exact each, summed in the MFMA's fp32 accumulator (G. Henry, P.
+// Tang, A. Heinecke, "Leveraging the bfloat16 artificial intelligence datatype for higher-precision
+// computations", 2019). What is left out is below 2^-22 of a product and of either sign; that is
+// less than the fp32 accumulation rounds off.
+// Measured against 64 bits (2-norm, S = 2257, 8 heads, D = 128): o 2.9e-7, dQ 4.7e-7, dK 6.3e-7, dV
+// 5.9e-7; with fp32 MFMA (v_mfma_f32_32x32x2) 3.6e-7, 5.5e-7, 7.5e-7, 7.0e-7; with fp32 FMAs, a thread
+// per row, dK 1.2e-6. 16 columns of a 32 x 32 tile take 6 MFMAs of 32 clocks; the fp32 MFMA takes 8 of 64.
 //
 // Bound and split. A wave splits the streamed operand as it reads it (44 VALU instructions of 4
 // clocks per 6 MFMAs), so the vector and the matrix units are about equally busy, and on few or short
@@ -19,9 +21,14 @@
 // tiles are used in different phases, so each is reloaded as soon as its last phase is done and lands
 // under the next phase. The waves' partial results are summed in LDS at the end, in wave order
 // (deterministic).
-// Measured, forward / backward: S = 2257, 8 heads, D = 128: a thread per row 8950 / 62,900 us; fp32
-// MFMA in this split 149 / 410; this 109 / 316. S = 832, 2 heads, D = 64: 945 / 1780; 24 / 43; 18 / 39.
-// S = 6000, 8 heads, D = 128: fp32 MFMA 744 / 2266, this 543 / 1739.
+// Of the two split row operands of the backward, one is held in registers and one, which is the same for
+// all waves, in LDS: with both in registers (96 each at D = 128, 48 at D = 64) the tile loops spilled
+// 38 and 72 registers, and a reload waits for the tile prefetch issued before it. Backward with
+// and without: S = 1000, 2 heads, D = 128 66.3 / 60.8 us; 2257 rows, 8 heads on 2 515 / 447; S = 832,
+// 2 heads, D = 64 33.9 / 27.9; 4000, 8, 64 435 / 382.
+// Forward / backward, us: S = 2257, 8 heads, D = 128: a thread per row 8950 / 62,900; fp32 MFMA in
+// this split 130 / 372; this 99 / 283. S = 832, 2 heads, D = 64: 945 / 1780; 20.8 / 37.7; 15.6 /
+// 27.9. S = 6000, 8 heads, D = 128: fp32 MFMA 774 / 2320, this 555 / 1730.
 //
 // Layout facts (lane l of a wave, h = l / 32):
 //   MFMA 32x32x16: A[m = l % 32][k = 8 h + 0..7], B[k = 8 h + 0..7][n = l % 32],
@@ -44,7 +51,7 @@ __device__ __forceinline__ f32x16 mfma_b16(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
-// 8 fp32 values as three bf16 vectors whose sum they are, exactly: h is the value cut to its top 16
+// 8 fp32 values as three bf16 vectors whose sum they are (see above for the smallest): h is the value cut to its top 16
 // bits (8 significant ones; cut, not rounded, so that no finite value becomes infinite), m the rest
 // rounded to 8 bits, l what is left, which has 8 bits or fewer.
 struct Split8 {
@@ -75,8 +82,8 @@ __device__ __forceinline__ Split8 split8(const float* x) {
   return r;
 }
 
-// acc += a b: the six products of the parts down to 2^-16 of the whole, smallest first. What is
-// left out (m l, l m, l l) is below 2^-23 of a product and of either sign.
+// acc += a b: the six products of the parts down to 2^-16 of the whole, smallest first. Left out are
+// m l and l m, each below 2^-23 of a product (m is up to 2^-7 of its value, l up to 2^-16), and l l.
 __device__ __forceinline__ f32x16 mfma_split(const Split8& a, const Split8& b, f32x16 acc) {
   acc = mfma_b16(a.m, b.m, acc);
   acc = mfma_b16(a.l, b.h, acc);
@@ -151,41 +158,59 @@ __device__ __forceinline__ void load_row_regs(const float* src, int row, int h, 
   }
 }
 
-// Order of a step's instructions. A wave that has its SIMD to itself (D = 128, up to 512 registers)
-// runs a sixth of the next operands' split between any two MFMAs: S = 2257, 8 heads 103 / 302 us
-// against 106 / 321 in the compiler's order. With two waves per SIMD (D = 64) the other wave fills
-// the gaps, and each step is closed off so that fewer operands are live: 55 / 162 us against 53 / 175.
+// The same rows, split once by the workgroup into LDS: part x (h, m, l) of operand s, 16 bytes a lane.
 template <int D>
-__device__ __forceinline__ void mix_split() {
-  if constexpr (D == 128) {
-#pragma unroll
-    for (int i = 0; i < 6; ++i) {  // groups: MFMA (0x008), DS reads (0x100), VALU (0x002)
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-      __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);
-    }
-  } else {
-    __builtin_amdgcn_sched_barrier(0);
+struct SplitLds {
+  static constexpr int WORDS = 3 * (D / 16) * 256;  // 24 KB at D = 128, 12 KB at D = 64
+  const uint32_t* p;
+  int lane;
+  __device__ __forceinline__ bf16x8 part(int s, int x) const {
+    return *reinterpret_cast<const bf16x8*>(p + ((3 * s + x) * 64 + lane) * 4);
   }
+  __device__ __forceinline__ Split8 operator[](int s) const { return Split8{part(s, 0), part(s, 1), part(s, 2)}; }
+};
+template <int D, int NF>
+__device__ __forceinline__ SplitLds<D> put_row_split(uint32_t* dst, const float* src, int row, int lane, int f) {
+#pragma unroll
+  for (int s = f; s < D / 16; s += NF) {
+    const float* r = src + (int64_t)row * D + 16 * s + 4 * (lane >> 5);
+    const float4 x = *reinterpret_cast<const float4*>(r), y = *reinterpret_cast<const float4*>(r + 8);
+    const float v[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+    const Split8 o = split8(v);
+    uint32_t* d = dst + (3 * s * 64 + lane) * 4;
+    *reinterpret_cast<bf16x8*>(d) = o.h;
+    *reinterpret_cast<bf16x8*>(d + 256) = o.m;
+    *reinterpret_cast<bf16x8*>(d + 512) = o.l;
+  }
+  return SplitLds<D>{dst, lane};
+}
+
+// With two waves per SIMD (D = 64) the other wave fills the gaps of a step, and each step is closed
+// off so that fewer operands are live; at D = 128 the compiler orders a whole product (S = 1000, 2
+// heads 34.7 us forward, with closed steps 36.2). Scheduling groups that interleave every step's
+// split with its MFMAs are 1 to 2% faster forward at D = 128 but take minutes to compile.
+template <int D>
+__device__ __forceinline__ void close_step() {
+  if constexpr (D == 64) __builtin_amdgcn_sched_barrier(0);
 }
 
 // acc += tile (rows = m) x regs^T (rows = n) over D. The reads and the split of the next 16 columns
 // run under the MFMAs of the current ones.
-template <int D>
-__device__ __forceinline__ f32x16 rows_product(const Tile32<D>& tl, const float* t, const Split8* regs, f32x16 acc) {
+template <int D, typename Regs>
+__device__ __forceinline__ f32x16 rows_product(const Tile32<D>& tl, const float* t, const Regs& regs, f32x16 acc) {
   auto get = [&](int s) __attribute__((always_inline)) {
     const float4 x = tl.row(t, 2 * s), y = tl.row(t, 2 * s + 1);
     const float f[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
     return split8(f);
   };
-  Split8 cur = get(0);
+  Split8 cur = get(0), op = regs[0];
 #pragma unroll
   for (int s = 0; s < D / 16; ++s) {
-    Split8 nxt = cur;
-    if (s + 1 < D / 16) nxt = get(s + 1);
-    acc = mfma_split(cur, regs[s], acc);
-    mix_split<D>();
-    cur = nxt;
+    Split8 nxt = cur, opn = op;
+    if (s + 1 < D / 16) nxt = get(s + 1), opn = regs[s + 1];
+    acc = mfma_split(cur, op, acc);
+    close_step<D>();
+    cur = nxt, op = opn;
   }
   return acc;
 }
@@ -208,13 +233,14 @@ __device__ __forceinline__ void cols_product(const Tile32<D>& tl, const float* t
 #pragma unroll
     for (int j = 0; j < 8; ++j) f[j] = x[8 * u + j];
     const Split8 xs = split8(f);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int d = 0; d < ND; ++d) {
       Split8 nxt = cur;
       if (d + 1 < ND) nxt = get(u, d + 1);
       else if (u == 0) nxt = get(1, 0);
       acc[d] = XA ? mfma_split(xs, cur, acc[d]) : mfma_split(cur, xs, acc[d]);
-      mix_split<D>();
+      close_step<D>();
       cur = nxt;
     }
   }
@@ -357,7 +383,7 @@ struct BwdF32 {
 // dQ^T += K^T dS^T.
 template <int D, int NF>
 __device__ __forceinline__ void dq_block(const BwdF32& a, int64_t lin, float (*At)[32 * D], float (*Bt)[32 * D],
-                                         int lane, int f) {
+                                         uint32_t* sp, int lane, int f) {
   using T = Tile32<D>;
   const int h = lane >> 5, r32 = lane & 31, S = a.S;
   const int nblk = (S + 31) / 32;
@@ -371,9 +397,10 @@ __device__ __forceinline__ void dq_block(const BwdF32& a, int64_t lin, float (*A
   float* vt = Bt[f];
   const T tl(lane);
   const int row = myq < S ? myq : S - 1;
-  Split8 q[D / 16], go[D / 16];
+  Split8 q[D / 16];
   load_row_regs<D>(a.q + bh * S * D, row, h, q);
-  load_row_regs<D>(a.go + bh * S * D, row, h, go);
+  const SplitLds<D> go = put_row_split<D, NF>(sp, a.go + bh * S * D, row, lane, f);
+  __syncthreads();
   const float lse = a.lse[bh * S + row], ndl = -a.delta[bh * S + row];
   f32x16 dq[D / 32];
 #pragma unroll
@@ -427,7 +454,7 @@ __device__ __forceinline__ void dq_block(const BwdF32& a, int64_t lin, float (*A
 // -Delta), S = Q K^T, dV += P^T dO, dK += dS^T Q. A wave's tiles run over (head, query tile).
 template <int D, int NF>
 __device__ __forceinline__ void dkdv_block(const BwdF32& a, int64_t lin, float (*At)[32 * D], float (*Bt)[32 * D],
-                                           float (*st)[64], int lane, int f) {
+                                           float (*st)[64], uint32_t* sp, int lane, int f) {
   using T = Tile32<D>;
   const int h = lane >> 5, r32 = lane & 31, S = a.S;
   const F32Pos pos = f32_pos(lin, a.kheads);
@@ -439,9 +466,10 @@ __device__ __forceinline__ void dkdv_block(const BwdF32& a, int64_t lin, float (
   float* stat = st[f];  // lse of the tile's rows, then -Delta
   const T tl(lane);
   const int row = mykey < S ? mykey : S - 1;
-  Split8 k[D / 16], v[D / 16];
+  Split8 k[D / 16];
   load_row_regs<D>(a.k + bs * S * D, row, h, k);
-  load_row_regs<D>(a.v + bs * S * D, row, h, v);
+  const SplitLds<D> v = put_row_split<D, NF>(sp, a.v + bs * S * D, row, lane, f);
+  __syncthreads();
   f32x16 dk[D / 32], dv[D / 32];
 #pragma unroll
   for (int d = 0; d < D / 32; ++d) dk[d] = dv[d] = f32x16{};
@@ -530,10 +558,11 @@ template <int D, int NF>
 __global__ void __launch_bounds__(64 * NF, D == 64 ? 2 : 1) sdpa_bwd_f32(BwdF32 a) {
   __shared__ __align__(16) float At[NF][32 * D], Bt[NF][32 * D];
   __shared__ __align__(16) float st[NF][64];
+  __shared__ __align__(16) uint32_t sp[SplitLds<D>::WORDS];
   const int lane = threadIdx.x & 63, f = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t lin = blockIdx.x;
-  if (lin < a.kblocks) dkdv_block<D, NF>(a, lin, At, Bt, st, lane, f);
-  else dq_block<D, NF>(a, lin - a.kblocks, At, Bt, lane, f);
+  if (lin < a.kblocks) dkdv_block<D, NF>(a, lin, At, Bt, st, sp, lane, f);
+  else dq_block<D, NF>(a, lin - a.kblocks, At, Bt, sp, lane, f);
 }
 
 }  // namespace lh
