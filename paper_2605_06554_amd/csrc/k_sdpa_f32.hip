@@ -569,9 +569,13 @@ __global__ void __launch_bounds__(64 * NF, D == 64 ? 2 : 1) sdpa_bwd_f32(BwdF32 
 
 using namespace lh;
 
-// Waves per workgroup: 4 at D = 128 (128 KB of tiles); at D = 64, 8 (the same 128 KB) while the
-// row blocks alone do not fill the chip, else 4 (64 KB, two workgroups per CU).
-static bool few_blocks(int64_t blocks) { return blocks <= 256; }
+// Waves per workgroup at D = 64 (at D = 128 4, with 128 KB of tiles): 8 (the same 128 KB, one
+// workgroup per CU) where the row blocks leave CUs idle, else 4 (64 KB, two per CU). Forward, 8 and 4
+// waves: 284 blocks (S = 2257, 4 heads) 34.7 and 41.0 us, 497 43.1 and 46.4, 528 54.4 and 57.1, 568
+// 52.2 and 50.8, 1000 133 and 124. Backward, over the blocks of dK/dV and dQ: 456 53.3 and 72.4, 568
+// 82.3 and 96.7, 710 99.5 and 95.0, 1136 150 and 144.
+static bool eight_waves_fwd(int64_t blocks) { return blocks <= 544; }
+static bool eight_waves_bwd(int64_t blocks) { return blocks <= 640; }
 
 hipError_t lh_launch_sdpa_fwd_f32(const LhShape& s, const void* qs, const void* ks, const void* vs, void* os,
                                   float* lse, hipStream_t st) {
@@ -581,7 +585,7 @@ hipError_t lh_launch_sdpa_fwd_f32(const LhShape& s, const void* qs, const void* 
   if (s.D == 128)
     hipLaunchKernelGGL((sdpa_fwd_f32<128, 4>), grid, dim3(256), 0, st, q, k, v, (float*)os, lse, (int)s.S, s.scale,
                        s.Hq, s.Hs, s.Gq);
-  else if (few_blocks(blocks))
+  else if (eight_waves_fwd(blocks))
     hipLaunchKernelGGL((sdpa_fwd_f32<64, 8>), grid, dim3(512), 0, st, q, k, v, (float*)os, lse, (int)s.S, s.scale,
                        s.Hq, s.Hs, s.Gq);
   else
@@ -600,7 +604,7 @@ hipError_t lh_launch_sdpa_bwd_f32(const LhShape& s, const void* qs, const void* 
   const int64_t blocks = nblk * (s.B * s.Hs + s.B * s.Hq);
   const dim3 grid((unsigned)blocks);
   if (s.D == 128) hipLaunchKernelGGL((sdpa_bwd_f32<128, 4>), grid, dim3(256), 0, st, a);
-  else if (few_blocks(blocks)) hipLaunchKernelGGL((sdpa_bwd_f32<64, 8>), grid, dim3(512), 0, st, a);
+  else if (eight_waves_bwd(blocks)) hipLaunchKernelGGL((sdpa_bwd_f32<64, 8>), grid, dim3(512), 0, st, a);
   else hipLaunchKernelGGL((sdpa_bwd_f32<64, 4>), grid, dim3(256), 0, st, a);
   return hipGetLastError();
 }
