@@ -1,7 +1,8 @@
 """The selection where the radix select changes course: a first digit whose bin holds just as many
 keys as are ranked outright (256), one more, or nearly all keys (further digits follow), with and
-without ties at the threshold, in every key store (LDS with the lists, LDS, global) and in chunks.
-Exact against the oracle."""
+without ties at the threshold, in every key store (LDS with the lists, LDS, global) and in chunks;
+and the order kernel on both sides of the line between its ranges of 1024 and 8192 window ends, where
+the ranges' edges split coarse windows. Exact against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -43,3 +44,26 @@ def test_bin_sizes(N, p, L, k, flags, inbin, ties, rng):
     ri, rs = oracle.select(oracle.Head(N, 64, p, L, k, oracle.F32, flags), s, np.zeros(Ptot, np.float32))
     check_equal("idx", idx[0, 0].cpu().numpy(), ri)
     check_equal("slot", slot[0, 0].cpu().numpy(), rs)
+
+
+@pytest.mark.parametrize("flags", [0, 1])
+@pytest.mark.parametrize("N,p,L,k,H", [(20000, 5, 3, 300, 85), (20000, 5, 3, 300, 86), (9999, 3, 3, 200, 128),
+                                       (19683, 3, 5, 50, 86), (16400, 2, 5, 40, 86)])
+def test_order_ranges(N, p, L, k, H, flags, rng):
+    """Selections x ranges of 8192 window ends: 255 (ranges of 1024 run) and 256 or more; with p = 3 and
+    5 a range's edge lies inside windows of every level; at N = 16,400 the last range holds one window."""
+    print(f"[select edges order] N={N} p={p} L={L} k={k} H={H} flags={flags}", flush=True)
+    N -= N % p ** (L - 1)
+    pr = lh.problem(1, N, H, H, 64, p, L, k, lh.LH_F32, 0.0, flags)
+    S, Ptot = lh.lh_subseq_len(pr), lh.lh_pyramid_rows(pr)
+    s = rng.random((H, Ptot)).astype(np.float32)
+    sq = torch.from_numpy(s).view(1, H, Ptot).to(DEV)
+    idx = torch.empty(1, H, S, dtype=torch.int32, device=DEV)
+    slot = torch.empty(1, H, Ptot, dtype=torch.int32, device=DEV)
+    lh.lh_select_topk(pr, sq, torch.zeros_like(sq), idx, slot, lh.workspace(pr, lh.LH_OP_SELECT))
+    torch.cuda.synchronize()
+    head = oracle.Head(N, 64, p, L, k, oracle.F32, flags)
+    for h in range(H):
+        ri, rs = oracle.select(head, s[h], np.zeros(Ptot, np.float32))
+        check_equal(f"idx[{h}]", idx[0, h].cpu().numpy(), ri)
+        check_equal(f"slot[{h}]", slot[0, h].cpu().numpy(), rs)

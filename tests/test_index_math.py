@@ -6,7 +6,7 @@ recomputes each launcher's grid and the per-thread index arithmetic of
 
     gather_kernel; scatter_long_kernel, scatter_kernel; gather_bwd_long_kernel,
     gather_bwd_group_long_kernel (packed and not), gather_bwd_group_kernel, gather_bwd_kernel;
-    scatter_bwd_kernel; pool_score_kernel; the selection workspace of select_kernel and
+    scatter_bwd_leaf_kernel, scatter_bwd_kernel; pool_leaf_kernel, pool_score_kernel; the selection workspace of select_kernel and
     order_kernel
 
 from the formulas of their sources, and asserts:
@@ -81,6 +81,9 @@ def _cases():
 
 
 CASES = _cases()
+
+# Window ends per workgroup of order_kernel: 8192, and 1024 where those are fewer than 256 workgroups.
+ORDER_RANGES = (1024, 8192)
 
 
 def inside(name, lo, hi, size):
@@ -395,33 +398,33 @@ def test_selection_workspace_math(name, c, flags):
     # of maxsel keys per selection after the lists
     if s.maxsel > 32768:
         inside("select key rows", BH * s.Scand, BH * s.Scand + BH * s.maxsel, ws_bytes // 4)
-    # order_kernel: grid ((N + 8191) / 8192, BH); workgroup x owns the window ends [e0, e1) and
+    # order_kernel: grid ((N + E - 1) / E, BH); workgroup x owns the window ends [e0, e1) and
     # the level-l entries [e0 // p^l, e1 // p^l): every pyramid entry's slot is written by
-    # exactly one workgroup, and its flag index (end - e0) L + (L - 1 - l) stays in [0, 8192 L)
-    E = 8192
-    gx = -(-s.N // E)
-    e0 = np.arange(gx, dtype=np.int64) * E
-    e1 = np.minimum(e0 + E, s.N)
-    assert e0.max() < 2 ** 31 and (e1 > e0).all()
-    for l in range(s.L):
-        lo, hi = e0 // s.pw[l], e1 // s.pw[l]
-        ids = np.concatenate([np.arange(a, b) for a, b in zip(lo, hi)])
-        once(f"order slot entries l{l}", ids, s.nrow[l])
-        blk = np.repeat(np.arange(gx), hi - lo)
-        x = ((ids + 1) * s.pw[l] - 1 - e0[blk]) * s.L + (s.L - 1 - l)
-        inside(f"order flag index l{l}", x, x + 1, E * s.L)
-    # the flag scan: 512 threads, thread t owns words [t CW, t CW + CW) clipped to the range's
-    # 8192 L / 32 words, so every word is scanned exactly once and ranks fit 16 bits
-    NW = E * s.L // 32
-    CW = -(-NW // 512)
-    own = np.concatenate([np.arange(t * CW, min(t * CW + CW, NW)) for t in range(512)])
-    once("order scan words", own, NW)
-    assert E * s.L <= 65536
+    # exactly one workgroup, and its flag index (end - e0) L + (L - 1 - l) stays in [0, E L)
+    for E in ORDER_RANGES:
+        gx = -(-s.N // E)
+        e0 = np.arange(gx, dtype=np.int64) * E
+        e1 = np.minimum(e0 + E, s.N)
+        assert e0.max() < 2 ** 31 and (e1 > e0).all()
+        for l in range(s.L):
+            lo, hi = e0 // s.pw[l], e1 // s.pw[l]
+            ids = np.concatenate([np.arange(a, b) for a, b in zip(lo, hi)])
+            once(f"order slot entries l{l}", ids, s.nrow[l])
+            blk = np.repeat(np.arange(gx), hi - lo)
+            x = ((ids + 1) * s.pw[l] - 1 - e0[blk]) * s.L + (s.L - 1 - l)
+            inside(f"order flag index l{l}", x, x + 1, E * s.L)
+        # the flag scan: 512 threads, thread t owns words [t CW, t CW + CW) clipped to the range's
+        # E L / 32 words, so every word is scanned exactly once and ranks fit 16 bits
+        NW = E * s.L // 32
+        CW = -(-NW // 512)
+        own = np.concatenate([np.arange(t * CW, min(t * CW + CW, NW)) for t in range(512)])
+        once("order scan words", own, NW)
+        assert E * s.L <= 65536
     # every emitted entry gets a distinct rank in [0, S)
     assert s.S <= s.Scand
 
 
-def _order_by_ranges(N, p, L, lists, replace, E=8192):
+def _order_by_ranges(N, p, L, lists, replace, E):
     """order_kernel's ranking, restated on the CPU: per range of window ends, the emitted
     entries before it (lower bounds in the sorted lists, less the parents below them in replace
     mode) plus an exclusive scan over the range's (end, level) flags."""
@@ -456,7 +459,9 @@ def _order_by_ranges(N, p, L, lists, replace, E=8192):
 @pytest.mark.parametrize("N,p,L,k,replace,seed", [(4096, 4, 4, 100, False, 1), (4096, 4, 4, 100, True, 2),
                                                   (3000, 5, 3, 40, False, 3), (3000, 5, 3, 40, True, 4),
                                                   (2048, 2, 8, 12, True, 5), (1000, 2, 1, 0, False, 6),
-                                                  (8192, 4, 5, 0, False, 7), (5120, 4, 3, 2000, True, 8)])
+                                                  (8192, 4, 5, 0, False, 7), (5120, 4, 3, 2000, True, 8),
+                                                  (20000, 5, 3, 300, False, 9), (20000, 5, 3, 300, True, 10),
+                                                  (19683, 3, 4, 500, True, 11)])
 def test_order_ranges_match_sorted_keys(N, p, L, k, replace, seed):
     """The range-wise ranking equals sorting the emitted entries by key = e L + (L - 1 - l),
     e = (i + 1) p^l - 1, for selections of the structure select_kernel writes (the coarsest
@@ -468,9 +473,10 @@ def test_order_ranges_match_sorted_keys(N, p, L, k, replace, seed):
         npar = min(k, len(lists[l]))
         par = np.sort(rng.choice(lists[l], npar, replace=False))
         lists[l - 1] = (par[:, None] * p + np.arange(p)[None, :]).ravel()
-    # the kernel's ranges of 8192 window ends, and short ones that split coarse windows
-    got = _order_by_ranges(N, p, L, lists, replace)
-    assert got == _order_by_ranges(N, p, L, lists, replace, E=64)
+    # the kernel's ranges of window ends, and short ones that split coarse windows
+    got = _order_by_ranges(N, p, L, lists, replace, 64)
+    for E in ORDER_RANGES:
+        assert got == _order_by_ranges(N, p, L, lists, replace, E)
     emitted = []
     for l in range(L):
         child = set(lists[l - 1].tolist()) if (replace and l >= 1) else set()
