@@ -547,17 +547,32 @@ def test_pool_leaf_index_math(name, c):
     assert WR % s.P == 0 or s.P == 1, "a pooling window would straddle two workgroups"
     nrow = -(-s.N // WR)
     nchunk = -(-nslots // HW)
-    lin = np.arange(min(nrow * nchunk, 1 << 16))
-    once("leaf workgroups", (lin // nchunk) * nchunk + lin % nchunk, lin.size)
-    # thread (rg, hs, cc): rows w0 + rg LR + b0 + r; rows at or past N are neither read nor written
+    # block lin: row range lin // nchunk, head slots slot0 .. slot0 + HW - 1; thread tid: chunk cc of
+    # slot hs, leaf rg
+    lin = np.arange(nrow * nchunk, dtype=np.int64)
+    rblk = lin // nchunk
+    slot = ((lin - rblk * nchunk) * HW)[:, None] + np.arange(HW)
+    once("leaf row ranges of every head slot", (rblk[:, None] * nslots + slot)[slot < nslots], nrow * nslots)
+    tid = np.arange(nt)
+    cc, grp = tid & (CPR - 1), tid >> s.cs
+    hs, rg = grp & (HW - 1), grp >> (HW.bit_length() - 1)
+    row = rg[:, None] * LR + np.arange(LR)  # of the workgroup's WR
+    once("leaf chunks", (hs[:, None] * WR + row) * CPR + cc[:, None], HW * WR * CPR)
+    # rows at or past N are neither read nor written
     rows = (np.arange(nrow)[:, None] * WR + np.arange(WR)[None, :]).ravel()
     once("leaf base rows", rows[rows < s.N], s.N)
-    # staged LDS row (hs RG + rg) BR + r, chunk cc; one norm thread per staged row
+    # staged LDS rows of D + CH elements, one norm thread per row: it stands for the row that the
+    # staging threads put there
     e = np.arange(HW * RG * BR)
-    hs, q = e // (RG * BR), e % (RG * BR)
+    e_slot, q = e // (RG * BR), e % (RG * BR)
     g, r = q // BR, q % BR
-    once("leaf staged rows", (hs * RG + g) * BR + r, HW * RG * BR)
-    score_at = np.concatenate([hs * WR + g * LR + b0 + r for b0 in range(0, LR, BR)])
+    for b0 in range(0, LR, BR):
+        at = ((hs * RG + rg) * BR)[:, None] + np.arange(BR)
+        once("leaf staged chunks", at * CPR + cc[:, None], HW * RG * BR * CPR)
+        end = (at.max() * (s.D + s.CH) + (CPR - 1) * s.CH) * s.es + 16
+        inside("leaf staged bytes", 0, end, HW * RG * BR * (s.D * s.es + 16))
+        assert (e_slot[at] == hs[:, None]).all() and ((g * LR + b0 + r)[at] == row[:, b0:b0 + BR]).all()
+    score_at = np.concatenate([e_slot * WR + g * LR + b0 + r for b0 in range(0, LR, BR)])
     once("leaf level-0 scores", score_at, HW * WR)
     base, nw, span = 0, WR, 1
     for l in range(1, s.L):
@@ -571,8 +586,14 @@ def test_pool_leaf_index_math(name, c):
         # rows of level l: the thread's own windows (l <= A) or one window per row group
         if l > A:
             assert n <= RG, "a row group per window"
-            kids = (np.arange(n)[:, None] * s.p + np.arange(s.p)).ravel()
-            assert kids.max() < (RG if l == A + 1 else nw)
+            # window i = rg adds the sums at the places of threads (i p + r, slot, chunk)
+            up = rg < n
+            kid = (rg[up, None] * s.p + np.arange(s.p)) * HW + hs[up, None]
+            child = (kid << s.cs) + cc[up, None]
+            inside("leaf sums", child, child + 1, nt)
+            assert (rg[child] // s.p == rg[up, None]).all() and (hs[child] == hs[up, None]).all()
+            assert (cc[child] == cc[up, None]).all()
+            once("leaf sums of a level", child, n * s.p * HW * CPR)
         w = (np.arange(nrow)[:, None] * (WR // span) + np.arange(n)[None, :]).ravel()
         valid = w * span < s.N
         once(f"leaf level-{l} windows", w[valid], s.nrow[l])
@@ -607,7 +628,17 @@ def test_scatter_bwd_leaf_index_math(name, c):
     head, cc0 = gs >> sub, (gs & ((1 << sub) - 1)) << cpr
     ok = head < s.Hq
     once("scatter_bwd chunks", ((head[ok] << s.cs) + cc0[ok])[:, None] + np.arange(CPR), s.Hq << s.cs)
+    # thread tid: chunk c0 of slot hs, leaf rg; block lin: positions lin // nchunk, the slots of one chunk
+    tid = np.arange(nt)
+    c0, grp = tid & (CPR - 1), tid >> cpr
+    hs, rg = grp & ((1 << sh) - 1), grp >> sh
+    once("scatter_bwd thread rows", ((hs * W)[:, None] + rg[:, None] * LR + np.arange(LR)) * CPR + c0[:, None],
+         (W << sh) * CPR)
     nblk = -(-U // W)
+    lin = np.arange(nblk * nchunk, dtype=np.int64)
+    rblk = lin // nchunk
+    slot = ((lin - rblk * nchunk) << sh)[:, None] + np.arange(1 << sh)
+    once("scatter_bwd ranges of every slot", (rblk[:, None] * nslots + slot)[slot < nslots], nblk * nslots)
     u = (np.arange(nblk)[:, None] * W + np.arange(W)).ravel()
     valid = (u >= 1) & (u <= s.N)
     once("scatter_bwd level-0 rows", u[valid] - 1, s.N)
@@ -618,5 +649,9 @@ def test_scatter_bwd_leaf_index_math(name, c):
         entry = w[(w >= 1) & (w <= s.nrow[l])] - 1
         once(f"scatter_bwd level-{l} entries", entry, s.nrow[l])
         if l > A:
-            kids = (np.arange(n)[:, None] * s.p + np.arange(s.p)).ravel()
-            once(f"scatter_bwd level-{l} children", kids, RG // s.p ** (l - 1 - A))
+            up = rg < n
+            child = ((((rg[up, None] * s.p + np.arange(s.p)) << sh) + hs[up, None]) << cpr) + c0[up, None]
+            inside("scatter_bwd sums", child, child + 1, nt)
+            assert (rg[child] // s.p == rg[up, None]).all() and (hs[child] == hs[up, None]).all()
+            assert (c0[child] == c0[up, None]).all()
+            once(f"scatter_bwd level-{l} children", child, (RG // s.p ** (l - 1 - A) << sh) * CPR)
