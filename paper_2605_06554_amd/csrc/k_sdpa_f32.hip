@@ -37,6 +37,10 @@
 //   16-byte reads). A product over the 32 rows of a tile takes rows 8 (i / 4) + 4 h + i % 4 for i =
 //   8 u .. 8 u + 7, so the accumulator elements of those i, split, are that step's operand.
 //
+// A non-finite element of row j reaches no row before j of o and dQ, and one of Q or dO no key after j in dK
+// and dV (contain). What it does reach is not finite, but may be NaN where fp32
+// arithmetic has an infinity: the parts of an infinity are infinity and NaN.
+//
 // LDS tiles: 32 rows of D floats, chunk c (16 bytes) of row r at position c ^ (r mod chunks), so
 // that the lanes reading one chunk of consecutive rows hit different banks.
 #include <float.h>
@@ -59,6 +63,7 @@ struct Split8 {
 };
 typedef __attribute__((__vector_size__(8 * sizeof(float)))) float f32x8;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4s;
+typedef __attribute__((__vector_size__(8 * sizeof(uint16_t)))) uint16_t u16x8;
 __device__ __forceinline__ Split8 split8(const float* x) {
   Split8 r;
   u32x4s hp;
@@ -246,6 +251,67 @@ __device__ __forceinline__ void cols_product(const Tile32<D>& tl, const float* t
   }
 }
 
+// Rows after a query are masked by P = 0 and dS = 0, which keeps finite values out but not an infinity or a
+// NaN (0 x NaN): on the tile that holds the diagonal, one non-finite row would reach the rows before it.
+// A wave therefore looks that tile over before its products: non-finite elements are cleared, and the
+// results of cols_product that an unmasked one belongs to are made infinite beforehand. (The products
+// over D need no mark: a row with a non-finite element has a non-finite lse or Delta.) XA = false: the tile
+// holds keys, masked after the query r32; XA = true: queries, masked before the key. Whole steps with and
+// without: N = 1024, 2 heads of 64 88.2 and 87.0 us; N = 4112, 8 / 2 heads of 128 462 and 458.
+template <int D>
+__device__ __forceinline__ bool tile_finite(const Tile32<D>& tl, const float* t) {
+  float c = 0.0f;
+#pragma unroll 4
+  for (int kk = 0; kk < D / 8; ++kk) {
+    const float4 x = tl.row(t, kk);  // 0 times a non-finite value is NaN
+    c = __builtin_fmaf(x.x, 0.0f, __builtin_fmaf(x.y, 0.0f, __builtin_fmaf(x.z, 0.0f, __builtin_fmaf(x.w, 0.0f, c))));
+  }
+  return __builtin_amdgcn_ballot_w64(c != 0.0f) == 0;
+}
+// Non-finite elements of the tile to 0; edge[c]: the first (XA: last) row with one in column 64 c + lane.
+template <int D, bool XA>
+__device__ __forceinline__ void clear_nonfinite(float* t, int lane, int* edge) {
+#pragma unroll
+  for (int c = 0; c < D / 64; ++c) {
+    const int col = 64 * c + lane;
+    edge[c] = XA ? -1 : 32;
+#pragma unroll 1
+    for (int k = 0; k < 32; ++k) {
+      float* x = t + k * D + (((col >> 2) ^ (k & (D / 4 - 1))) << 2) + (col & 3);
+      if (__builtin_isfinite(*x)) continue;
+      *x = 0.0f;
+      if (XA || edge[c] == 32) edge[c] = k;
+    }
+  }
+}
+// acc += 2^127 x 2^127 where the first (XA: last) cleared row of the column is unmasked, else 0 exactly.
+template <int D, bool XA>
+__device__ __forceinline__ void mark_nonfinite(const int* edge, int h, int r32, f32x16* acc) {
+#pragma unroll
+  for (int d = 0; d < D / 32; ++d) {
+    const int e = __shfl(edge[d >> 1], 32 * (d & 1) + r32, 64);
+#pragma unroll 1  // (unrolled, the comparisons are kept in registers across the tile loop)
+    for (int u = 0; u < 2; ++u) {
+      u16x8 bad, in;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int k = 8 * (2 * u + (j >> 2)) + 4 * h + (j & 3);
+        bad[j] = k == e ? 0x7f00 : 0;
+        in[j] = (XA ? k >= r32 : k <= r32) ? 0x7f00 : 0;
+      }
+      const bf16x8 x = __builtin_bit_cast(bf16x8, in), y = __builtin_bit_cast(bf16x8, bad);
+      acc[d] = XA ? mfma_b16(x, y, acc[d]) : mfma_b16(y, x, acc[d]);
+    }
+  }
+}
+template <int D, bool XA>
+__device__ __forceinline__ void contain(const Tile32<D>& tl, float* t, int lane, f32x16* acc) {
+  if (tile_finite<D>(tl, t)) return;
+  int edge[D / 64];
+  clear_nonfinite<D, XA>(t, lane, edge);
+  mark_nonfinite<D, XA>(edge, lane >> 5, lane & 31, acc);
+}
+
 // A wave's accumulators to LDS: unit u = 4 d + g holds elements 4 g .. 4 g + 3 of acc[d].
 template <int D>
 __device__ __forceinline__ void put_acc(float* dst, const f32x16* acc, int lane) {
@@ -305,6 +371,10 @@ sdpa_fwd_f32(const float* __restrict__ Q, const float* __restrict__ K, const flo
   }
   for (int t = f; t < nt; t += NF) {
     const int tn = t + NF < nt ? t + NF : t;  // the last tile is loaded once more, unused
+    if (t == nt - 1) {
+      wait_loads<0>();
+      contain<D, false>(tl, vt, lane, o);
+    }
     wait_loads<T::NL>();  // the K tile has landed
     f32x16 s = rows_product<D>(tl, kt, q, f32x16{});
     wait_lds_reads();
@@ -420,12 +490,12 @@ __device__ __forceinline__ void dq_block(const BwdF32& a, int64_t lin, float (*A
     wait_lds_reads();
     T::load(vt, Vh, 32 * tn, S, lane);
     wait_loads<T::NL>();  // K
+    if (t == nt - 1) contain<D, false>(tl, kt, lane, dq);
     f32x16 s = rows_product<D>(tl, kt, q, f32x16{});
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], a.scale, -lse) * kLog2eF);
-      if (t == nt - 1 && 32 * t + 8 * (i >> 2) + 4 * h + (i & 3) > myq) p = 0.0f;
-      s[i] = p * dp[i];
+      const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], a.scale, -lse) * kLog2eF);
+      s[i] = t == nt - 1 && 32 * t + 8 * (i >> 2) + 4 * h + (i & 3) > myq ? 0.0f : p * dp[i];
     }
     cols_product<D, false>(tl, kt, s, dq);
     wait_lds_reads();
@@ -494,7 +564,9 @@ __device__ __forceinline__ void dkdv_block(const BwdF32& a, int64_t lin, float (
   }
   for (int t = f; t < nt; t += NF) {
     const int tn = t + NF < nt ? t + NF : t;
+    const bool diag = t % ntq == 0;
     wait_loads<T::NL>();  // dO (and lse, Delta)
+    if (diag) contain<D, true>(tl, gt, lane, dv);
     const bool in = row_of(t) + r32 < S;  // rows past S: P = 0
     stat[lane] = h ? (in ? -sx : 0.0f) : (in ? sx : INFINITY);
     f32x16 dp;
@@ -505,8 +577,8 @@ __device__ __forceinline__ void dkdv_block(const BwdF32& a, int64_t lin, float (
     }
     dp = rows_product<D>(tl, gt, v, dp);
     wait_loads<0>();  // Q
+    if (diag) contain<D, true>(tl, qt, lane, dk);
     f32x16 s = rows_product<D>(tl, qt, k, f32x16{});
-    const bool diag = t % ntq == 0;
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       const float4 l4 = *reinterpret_cast<const float4*>(stat + 8 * g + 4 * h);
@@ -514,10 +586,10 @@ __device__ __forceinline__ void dkdv_block(const BwdF32& a, int64_t lin, float (
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int i = 4 * g + j;
-        float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], a.scale, -lv[j]) * kLog2eF);
-        if (diag && 8 * g + 4 * h + j < r32) p = 0.0f;
-        s[i] = p;
-        dp[i] *= p;
+        const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], a.scale, -lv[j]) * kLog2eF);
+        const bool masked = diag && 8 * g + 4 * h + j < r32;
+        s[i] = masked ? 0.0f : p;
+        dp[i] = masked ? 0.0f : p * dp[i];
       }
     }
     cols_product<D, true>(tl, gt, s, dv);

@@ -86,6 +86,54 @@ def test_fp32_shared(S, D, Hq, Hkv, B, rng):
 
 
 @pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("value", [float("nan"), float("inf"), float("-inf")])
+@pytest.mark.parametrize("S,j,Hq", [(97, 0, 2), (97, 40, 2), (97, 96, 2), (545, 301, 32)])
+def test_fp32_nonfinite_stays_causal(S, j, Hq, value, D):
+    """One non-finite element in row j of K, V, Q or dO: rows before j of o and dQ, and for Q and dO the
+    other rows and the keys after j of dK and dV, keep their bits; what depends on it is not finite."""
+    print(f"[sdpa edges non-finite] S={S} D={D} j={j} value={value}", flush=True)
+    Hs, col = Hq // 2, 37
+    pr = lh.problem(1, S, Hq, Hs, D, 2, 1, 0, torch.float32, flags=lh.LH_FLAG_GQA_SHARED)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(S + D)
+    x = [torch.randn(1, H, S, D, device=DEV, generator=g) for H in (Hq, Hs, Hs, Hq)]
+    ws = lh.workspace(pr, lh.LH_OP_SDPA_BWD)
+
+    def step(q, k, v, do):
+        o, dq, dk, dv = (torch.full_like(t, float("nan")) for t in (q, q, k, v))
+        lse = torch.empty(1, Hq, S, device=DEV)
+        lh.lh_sdpa_fwd(pr, q, k, v, o, lse)
+        lh.lh_sdpa_bwd(pr, q, k, v, o, lse, do, dq, dk, dv, ws)
+        torch.cuda.synchronize()
+        return o, dq, dk, dv
+
+    clean = step(*x)
+    assert all(bool(torch.isfinite(t).all()) for t in clean)
+    for n, name in enumerate(("q", "k", "v", "do")):
+        y = list(x)
+        y[n] = x[n].clone()
+        y[n][0, -1, j, col] = value  # the last head (of Q, dO: the last of its group)
+        o, dq, dk, dv = step(*y)
+        query = n in (0, 3)
+        for a, b, what in zip((o, dq, dk, dv), clean, ("o", "dq", "dk", "dv")):
+            H = a.shape[1]
+            hit = slice(H - 1, H) if query or what in ("dk", "dv") else slice(H - 2, H)
+            assert torch.equal(a[:, :hit.start], b[:, :hit.start]), (name, what, "another head")
+            a, b = a[0, hit], b[0, hit]
+            if what in ("o", "dq"):
+                assert torch.equal(a[:, :j], b[:, :j]), (name, what)
+                if query:
+                    assert torch.equal(a[:, j + 1:], b[:, j + 1:]), (name, what)
+            elif query:
+                assert torch.equal(a[:, j + 1:], b[:, j + 1:]), (name, what)
+        bad = lambda t: not bool(torch.isfinite(t).any())  # noqa: E731
+        if name == "v":
+            assert bad(o[0, -2:, j:, col]) and bad(dq[0, -2:, j:])
+        elif name == "do":
+            assert bad(dv[0, -1, :j + 1, col]) and bad(dq[0, -1, j]) and bad(dk[0, -1, :j + 1])
+
+
+@pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("S", [1, 33, 64, 65, 127, 128, 129, 257])
 def test_bf16_few_blocks(S, D, rng):
     """Few row blocks: a workgroup owns 64 rows, each 32-row block shared by 4 waves that take 32
