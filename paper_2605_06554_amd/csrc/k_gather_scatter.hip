@@ -1073,7 +1073,9 @@ static bool launch_scatter_bwd_leaf(const LhShape& s, const void* dout, const in
 template <typename T, int L>
 static bool launch_scatter_bwd_leaves(const LhShape& s, const void* dout, const int32_t* slot, void* dos,
                                       hipStream_t st) {
-  if (s.p == 4) return launch_scatter_bwd_leaf<T, 4, 2, L>(s, dout, slot, dos, st);
+  if (s.p == 4) {  // (4^7 positions are more than a workgroup holds)
+    if constexpr (L < 8) return launch_scatter_bwd_leaf<T, 4, 2, L>(s, dout, slot, dos, st);
+  }
   if (s.p == 3) return launch_scatter_bwd_leaf<T, 3, 2, L>(s, dout, slot, dos, st);
   if (s.p == 2) return launch_scatter_bwd_leaf<T, 2, 3, L>(s, dout, slot, dos, st);
   return false;

@@ -497,6 +497,14 @@ __global__ void __launch_bounds__(1024) pool_leaf_kernel(LeafArgs la) {
   }
 }
 
+// p^(L-1) rows fit a workgroup of leaves of LR rows, of the smallest head (D = 64).
+template <typename T>
+constexpr bool leaf_fits(int p, int LR, int L) {
+  int64_t P = 1;
+  for (int l = 1; l < L; ++l) P *= p;
+  return P / LR * (64 * (int)sizeof(T) / 16) <= 1024;
+}
+
 // Launches the leaf kernel with leaves of p^A rows; false if a workgroup cannot hold p^(L-1) rows.
 template <typename T, int P, int A, int BR>
 static bool launch_leaf(const LhShape& s, PoolArgs a, hipStream_t st) {
@@ -535,7 +543,8 @@ static bool launch_leaf(const LhShape& s, PoolArgs a, hipStream_t st) {
   constexpr int L0 = A == 3 && P > 2 ? 6 : 1;  // leaves of p^3 rows serve deep pyramids only
 #define LH_LEAF_CASE(LL)                                                                             \
   case LL:                                                                                           \
-    if constexpr (LL >= L0) hipLaunchKernelGGL((pool_leaf_kernel<T, P, A, BR, LL>), grid, block, shm, st, la); \
+    if constexpr (LL >= L0 && leaf_fits<T>(P, LR, LL))                                               \
+      hipLaunchKernelGGL((pool_leaf_kernel<T, P, A, BR, LL>), grid, block, shm, st, la);             \
     break;
   switch (s.L) {
     LH_LEAF_CASE(1)

@@ -286,7 +286,6 @@ __device__ __forceinline__ void store_qrow(bf16_t* row, const f32x16* acc, float
 
 // Ring slots are separate __shared__ arrays (not one indexed array), so the compiler can tell
 // that a load streaming into one slot does not alias reads of another and does not wait for it.
-template <int N>
 struct Ring {  // two slots of two operands
   bf16_t *a0, *a1, *b0, *b1;
   template <int SL>
@@ -329,7 +328,7 @@ constexpr bool kSplitAt = F > 1 || !IDX;
 // at a time. A unit is 4 accumulator elements: out(d, g, x) receives elements 4 g .. 4 g + 3 of
 // column block d, each unit in one of the F waves. wt[x]: weight of wave x's partial.
 template <int D, int F, int R, typename Out>
-__device__ __forceinline__ void combine(const Ring<0>& ring, const f32x16* acc, const float* wt, int w, int lane,
+__device__ __forceinline__ void combine(const Ring& ring, const f32x16* acc, const float* wt, int w, int lane,
                                         Out&& out) {
   constexpr int ND = D / 32 * F / 4;  // column blocks per round: a wave's share is half a slot
   constexpr int NU = 4 * ND / F;      // units per wave and round
@@ -604,7 +603,7 @@ sdpa_fwd_bf16(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const 
     }
     const float inv = 1.0f / l;
     bf16_t* orow = O + (bh * S + myq) * D;
-    combine<D, F, FR>(Ring<0>{Ks0, Ks1, Vs0, Vs1}, oacc, wt, w, lane, [&](int d, int g, const float* v) {
+    combine<D, F, FR>(Ring{Ks0, Ks1, Vs0, Vs1}, oacc, wt, w, lane, [&](int d, int g, const float* v) {
       if (myq < S) store_quad(orow + 32 * d + 8 * g + 4 * h, v, inv);
     });
     if (myq < S && f == 0 && h == 0) LSE[bh * S + myq] = (m_row + __log2f(l)) * kLn2;
@@ -685,7 +684,7 @@ sdpa_fwd_bf16(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const 
 // P = exp2(S scale log2e - lse log2e) and dS = P (dP - Delta); dQ^T += K^T dS^T.
 template <int D, bool IDX, int F>
 __device__ __forceinline__ void
-dq_block(const BlockPos bp, const Ring<0> ring, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
+dq_block(const BlockPos bp, const Ring ring, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
          const bf16_t* __restrict__ V, const bf16_t* __restrict__ dO, const float* __restrict__ LSE,
          const float* __restrict__ DELTA, bf16_t* __restrict__ dQ, int S, float sl2, float scale, const SdpaIdx& ix,
          const HeadMap& hm) {
@@ -825,7 +824,7 @@ dq_block(const BlockPos bp, const Ring<0> ring, const bf16_t* __restrict__ Q, co
 // over those heads (one pass of the query-tile loop per head, the accumulators kept).
 template <int D, bool IDX, bool GRP, int F>
 __device__ __forceinline__ void
-dkdv_block(const BlockPos bp, const Ring<0> ring, float* const ls0, float* const ls1, float* const ds0,
+dkdv_block(const BlockPos bp, const Ring ring, float* const ls0, float* const ls1, float* const ds0,
            float* const ds1, bf16_t* const Kw, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
            const bf16_t* __restrict__ V, const bf16_t* __restrict__ dO, const float* __restrict__ LSE,
            const float* __restrict__ DELTA, bf16_t* __restrict__ dK, bf16_t* __restrict__ dV, int S, float sl2,
@@ -1062,7 +1061,7 @@ sdpa_bwd_bf16(BwdArgs a, SdpaIdx ix, HeadMap hm) {
   __shared__ __align__(64) bf16_t A0[CQ * D], A1[CQ * D], B0[CQ * D], B1[CQ * D];
   __shared__ __align__(16) bf16_t Kw[CK * D];
   const uint32_t lin = blockIdx.x;
-  const Ring<0> ring{A0, A1, B0, B1};
+  const Ring ring{A0, A1, B0, B1};
   if (lin < a.kblocks)
     dkdv_block<D, IDX, GRP, F>(block_pos(lin, a.kheads), ring, ls0, ls1, ds0, ds1, Kw, a.q, a.k, a.v, a.go, a.lse,
                                a.delta, a.dk, a.dv, a.S, a.sl2, a.scale, ix, hm);
