@@ -45,6 +45,8 @@
 // that the lanes reading one chunk of consecutive rows hit different banks.
 #include <float.h>
 
+#include <type_traits>
+
 #include "lh_common.h"
 
 namespace lh {
@@ -256,8 +258,9 @@ __device__ __forceinline__ void cols_product(const Tile32<D>& tl, const float* t
 // A wave therefore looks that tile over before its products: non-finite elements are cleared, and the
 // results of cols_product that an unmasked one belongs to are made infinite beforehand. (The products
 // over D need no mark: a row with a non-finite element has a non-finite lse or Delta.) XA = false: the tile
-// holds keys, masked after the query r32; XA = true: queries, masked before the key. Whole steps with and
-// without: N = 1024, 2 heads of 64 88.2 and 87.0 us; N = 4112, 8 / 2 heads of 128 462 and 458.
+// holds keys, masked after the query r32; XA = true: queries, masked before the key. The backward does so in its
+// tile loop (4000 rows, 8 heads of 64 368 -> 372 us, others within 0.3%). In the forward that cost 3 to 5%;
+// there the wave looks its sums over at the end and forms them again where it has to.
 template <int D>
 __device__ __forceinline__ bool tile_finite(const Tile32<D>& tl, const float* t) {
   float c = 0.0f;
@@ -266,6 +269,15 @@ __device__ __forceinline__ bool tile_finite(const Tile32<D>& tl, const float* t)
     const float4 x = tl.row(t, kk);  // 0 times a non-finite value is NaN
     c = __builtin_fmaf(x.x, 0.0f, __builtin_fmaf(x.y, 0.0f, __builtin_fmaf(x.z, 0.0f, __builtin_fmaf(x.w, 0.0f, c))));
   }
+  return __builtin_amdgcn_ballot_w64(c != 0.0f) == 0;
+}
+template <int D>
+__device__ __forceinline__ bool sums_finite(const f32x16* acc) {
+  float c = 0.0f;
+#pragma unroll
+  for (int d = 0; d < D / 32; ++d)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) c = __builtin_fmaf(acc[d][i], 0.0f, c);
   return __builtin_amdgcn_ballot_w64(c != 0.0f) == 0;
 }
 // Non-finite elements of the tile to 0; edge[c]: the first (XA: last) row with one in column 64 c + lane.
@@ -359,57 +371,64 @@ sdpa_fwd_f32(const float* __restrict__ Q, const float* __restrict__ K, const flo
   Split8 q[D / 16];
   load_row_regs<D>(Q + bh * S * D, myq < S ? myq : S - 1, h, q);
   f32x16 o[D / 32];
-#pragma unroll
-  for (int d = 0; d < D / 32; ++d) o[d] = f32x16{};
-  // the running maximum of the unscaled logits starts at the lowest finite value: a masked logit
-  // (-inf) of a row without any key yet then has weight exp2(-inf) = 0
-  float m = -FLT_MAX, l = 0.0f;
+  float m, l;
   const int nt = qb + 1;  // key tiles 0 .. qb; only the last is masked
-  if (f < nt) {
-    T::load(kt, Kh, 32 * f, S, lane);
-    T::load(vt, Vh, 32 * f, S, lane);
-  }
-  for (int t = f; t < nt; t += NF) {
-    const int tn = t + NF < nt ? t + NF : t;  // the last tile is loaded once more, unused
-    if (t == nt - 1) {
-      wait_loads<0>();
-      contain<D, false>(tl, vt, lane, o);
+  auto pass = [&](auto again) __attribute__((always_inline)) {
+#pragma unroll
+    for (int d = 0; d < D / 32; ++d) o[d] = f32x16{};
+    // the running maximum of the unscaled logits starts at the lowest finite value: a masked logit
+    // (-inf) of a row without any key yet then has weight exp2(-inf) = 0
+    m = -FLT_MAX, l = 0.0f;
+    if (f < nt) {
+      T::load(kt, Kh, 32 * f, S, lane);
+      T::load(vt, Vh, 32 * f, S, lane);
     }
-    wait_loads<T::NL>();  // the K tile has landed
-    f32x16 s = rows_product<D>(tl, kt, q, f32x16{});
-    wait_lds_reads();
-    T::load(kt, Kh, 32 * tn, S, lane);
-    if (t == nt - 1) {
+    for (int t = f; t < nt; t += NF) {
+      const int tn = t + NF < nt ? t + NF : t;  // the last tile is loaded once more, unused
+      if (decltype(again)::value && t == nt - 1) {
+        wait_loads<0>();
+        contain<D, false>(tl, vt, lane, o);
+      }
+      wait_loads<T::NL>();  // the K tile has landed
+      f32x16 s = rows_product<D>(tl, kt, q, f32x16{});
+      wait_lds_reads();
+      T::load(kt, Kh, 32 * tn, S, lane);
+      if (t == nt - 1) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i)
-        if (32 * t + 8 * (i >> 2) + 4 * h + (i & 3) > myq) s[i] = -INFINITY;
+        for (int i = 0; i < 16; ++i)
+          if (32 * t + 8 * (i >> 2) + 4 * h + (i & 3) > myq) s[i] = -INFINITY;
+      }
+      float mx = s[0];
+#pragma unroll
+      for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      if (__builtin_amdgcn_ballot_w64(mx > m) != 0) {
+        const float mn = fmaxf(m, mx), al = __builtin_amdgcn_exp2f((m - mn) * sl2);
+        l *= al;
+#pragma unroll
+        for (int d = 0; d < D / 32; ++d)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) o[d][i] *= al;
+        m = mn;
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[i] = __builtin_amdgcn_exp2f((s[i] - m) * sl2);
+      float sum = 0.0f;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) sum += s[i];
+      l += sum;
+      wait_loads<T::NL>();  // the V tile has landed
+      cols_product<D, false>(tl, vt, s, o);
+      wait_lds_reads();
+      T::load(vt, Vh, 32 * tn, S, lane);
     }
-    float mx = s[0];
-#pragma unroll
-    for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    if (__builtin_amdgcn_ballot_w64(mx > m) != 0) {
-      const float mn = fmaxf(m, mx), al = __builtin_amdgcn_exp2f((m - mn) * sl2);
-      l *= al;
-#pragma unroll
-      for (int d = 0; d < D / 32; ++d)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) o[d][i] *= al;
-      m = mn;
-    }
-#pragma unroll
-    for (int i = 0; i < 16; ++i) s[i] = __builtin_amdgcn_exp2f((s[i] - m) * sl2);
-    float sum = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) sum += s[i];
-    l += sum;
-    wait_loads<T::NL>();  // the V tile has landed
-    cols_product<D, false>(tl, vt, s, o);
-    wait_lds_reads();
-    T::load(vt, Vh, 32 * tn, S, lane);
-  }
+    wait_loads<0>();
+  };
+  pass(std::false_type{});
+  // the wave of the masked tile forms its sums once more, with that tile contained, where they hold
+  // what is not finite
+  if (f == (nt - 1) % NF && !sums_finite<D>(o)) pass(std::true_type{});
   l += __shfl_xor(l, 32, 64);
-  wait_loads<0>();
   put_acc<D>(kt, o, lane);
   if (h == 0) ms[f][r32] = m, ls[f][r32] = l;
   __syncthreads();
