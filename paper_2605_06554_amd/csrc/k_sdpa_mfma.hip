@@ -1034,7 +1034,7 @@ dkdv_block(const BlockPos bp, const Ring ring, float* const ls0, float* const ls
 // dK/dV and dQ workgroups in one launch: they are independent and of one shape (8 waves, one
 // workgroup per CU at D = 128), so the long dQ blocks fill the CUs that the last dK/dV blocks
 // leave idle. Against two launches, F = 1: S = 2000, 8 heads 169 -> 103 us; 18,432, 8 heads 2161
-// -> 2065; 10,752, 32 heads on 8 selections 3477 -> 2910; no difference on a full chip (54,272, 32
+// -> 2060; 10,752, 32 heads on 8 selections 3475 -> 2950 to 3010 (the call alone); no difference on a full chip (54,272, 32
 // heads). Alternating the ranks of dK/dV and dQ blocks instead of all dK/dV first was slower
 // (18,432, 8 heads 2269): the blocks running together then stream more different tiles through
 // each L2. LDS is shared by name: dQ's K / V ring is dK/dV's Q / dO ring.
@@ -1071,24 +1071,31 @@ sdpa_bwd_bf16(BwdArgs a, SdpaIdx ix, HeadMap hm) {
 }
 
 // The split F of a launch (FwdCfg, BwdCfg) by the number of 32-row blocks of all heads, from
-// sweeps of S = 100 .. 30,000 rows and 2 .. 32 heads at D = 64 and 128 (the lines are the same).
-// Forward: a block of F = 1 needs 2.2 us per 64 keys (D = 128), F = 2 1.06 us, F = 4 1.47 us per
-// 128; a full chip does 2.1, 1.8 and 1.4 G pairs per ms. At 1248 blocks (S = 5000, 8 heads) F = 1,
-// 2, 4 take 174, 92, 95 us; at 768 (3000, 8) 110, 58, 43; at 3000 (12,000, 8) 422, 360, 420; at
-// 4608 (18,432, 8) 726, 761, 934.
+// sweeps of S = 2000 .. 24,000 rows and 1 .. 28 heads at D = 64 and 128, every F timed in turn.
+// Forward, us for F = 1, 2, 4 (the lines are the same at both D). F = 4 to 2, D = 128: 1099 blocks (5000
+// rows, 7 heads) 172, 84.5, 82.2; 1125 (12,000, 3) 400, 194, 174; 1222 (3000, 13) 105, 54.7, 65.5; 1256
+// (5000, 8) 171, 83.9, 85.4; D = 64: 1128 (3000, 12) 72.8, 36.7, 35.5; 1222 76.1, 37.6, 39.3; 1256 118,
+// 58.6, 56.6. F = 2 to 1, D = 128: 3375 (12,000, 9) 448, 402, 515; 3760 (6000, 20) 226, 219, 278; 4125 (12,000, 11)
+// 473, 482, 628; 4500 472, 499, 608; D = 64: 3760 150, 145, 172; 4136 (6000, 22) 153, 162, 193.
 static int fwd_split(const LhShape& s) {
   const int64_t nb = (s.S + 31) / 32 * s.B * s.Hq;
-  return nb <= 1280 ? 4 : nb <= 3400 ? 2 : 1;
+  return nb <= 1150 ? 4 : nb <= 3950 ? 2 : 1;
 }
-// Backward (dK/dV and dQ together): at 504 blocks (S = 2000, 8 heads) 103, 70, 60 us; at 752
-// (3000, 8) 148, 101, 109; at 1248 (5000, 8) 251, 204, 236; at 1500 (3000, 16) 165, 173, 220. With
-// a shared selection a dK/dV block is Gq times as long, so the lines lie further out: at 672
-// blocks of 4 query heads each (10,752 rows, 2 selections) 1940, 1153, 968; at 1344 (10,752, 4)
-// 2192, 1621, 1841; at 2304 (18,432, 4) 4434, 4708, 5330.
+// Backward (dK/dV and dQ together), us for F = 1, 2, 4. F = 4 to 2, D = 128: 504 blocks (2000 rows, 8 heads)
+// 95.2, 62.9, 54.7; 567 96.6, 65.5, 66.8; 630 96.2, 65.1, 70.1; at D = 64 the line lies further out: 567 61.1,
+// 40.9, 37.0; 625 (4000, 5) 113, 70.3, 60.8; 693 61.9, 41.5, 43.0; 756 61.0, 40.5, 45.0. F = 2 to 1, D = 128:
+// 1500 (8000, 6) 392, 344, 420; 1598 (3000, 17) 159, 161, 225; 1625 (4000, 13) 209, 208, 279; 1692 160, 167,
+// 221; D = 64: 1500 233, 198, 220; 1625 125, 121, 143; 1692 95.3, 98.2, 118.
+// With a shared selection a dK/dV block is Gq times as long, so the lines lie further out. 4 query
+// heads each, D = 128: 672 blocks (10,752 rows, 2 selections) 1975, 1130, 950; 750 (4000, 6) 752, 446, 465;
+// 1680 (10,752, 5) 2274, 2077, 2528; 2000 (4000, 16) 892, 971, 1166; 2016 (10,752, 6) 2345, 2438, 2907; D =
+// 64: 750 468, 263, 241; 1000 (4000, 8) 470, 290, 312; 2000 505, 517, 596; 2016 1395, 1329, 1533; 2352
+// (10,752, 7) 1492, 1570, 1820.
 static int bwd_split(const LhShape& s) {
   const int64_t nb = (s.S + 31) / 32 * s.B * s.Hs;
-  if (s.Gq > 1) return nb <= 800 ? 4 : nb <= 2100 ? 2 : 1;
-  return nb <= 560 ? 4 : nb <= 1450 ? 2 : 1;
+  const bool d64 = s.D == 64;
+  if (s.Gq > 1) return nb <= (d64 ? 800 : 710) ? 4 : nb <= (d64 ? 2100 : 1850) ? 2 : 1;
+  return nb <= (d64 ? 640 : 560) ? 4 : nb <= 1640 ? 2 : 1;
 }
 
 template <int D, bool IDX, int F>
