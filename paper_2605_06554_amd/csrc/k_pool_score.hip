@@ -572,15 +572,20 @@ static void launch_L(const PoolArgs& a, dim3 grid, dim3 block, size_t shm, hipSt
 }
 
 // Leaves of 16, 9 or 8 rows (p = 4, 3, 2); of 64 (p = 4) where p^(L-1) rows take more than 1024
-// threads. The walk over p^(L-1) rows stays for p > 4, for pyramids too deep for a workgroup, and
-// where a workgroup would be one head slot of more than 512 threads although the walk has 2048
-// workgroups or more: at N = 1,048,576, 48 slots, p = 4, L = 6 it takes 3.41 ms, leaves 3.87; at N
-// = 65,536, 6 slots 0.50 ms and 0.048.
+// threads. The walk over p^(L-1) rows stays for p > 4, for pyramids too deep for a workgroup, and in
+// bf16 where a workgroup of leaves would be one head slot of 1024 threads (L = 6, D = 128) although the
+// walk fills the chip, three workgroups a CU, and its chunks of 16 slots are full to an eighth. Walk and
+// leaves, us, by the walk's workgroups: 48 slots, 576 945 and 782; 672 960 and 903; 768 974 and 1034; 1024 1369
+// and 1366; 2048 2525 and 2713; 4096 4899 and 5445; 16, 32, 64 and 80 slots alike (768 0.95 to 0.97 of
+// the time, 4096 0.85 to 0.92); with chunks half or two thirds full, 24 slots, 768 878 and 768; 4096 4384 and
+// 4072; 40 slots 4565 and 4536. In fp32 leaves are as fast or faster (48 slots, 1536 3190 and 3160; 24, 2048
+// 3203 and 3097), and of 64 rows too (L = 7, N = 4,194,304, 48 slots 17.1 and 16.7 ms; D = 64 11.4 and 10.8).
 template <typename T>
 static bool launch_leaves(const LhShape& s, const PoolArgs& a, hipStream_t st) {
   if (s.p == 4) {
-    const int64_t walk = s.N / s.P * ((a.nslots + 15) / 16) * s.B;
-    if (s.P / 16 * (s.D * (int)sizeof(T) / 16) > 512 && walk >= 2048) return false;
+    const int64_t chunks = (a.nslots + 15) / 16, walk = s.N / s.P * chunks * s.B;
+    const bool full = chunks * 16 * 8 <= a.nslots * 9;
+    if (sizeof(T) == 2 && s.P / 16 * (s.D / 8) == 1024 && full && walk >= 720) return false;
     return launch_leaf<T, 4, 2, 8>(s, a, st) || (s.L >= 6 && launch_leaf<T, 4, 3, 8>(s, a, st));
   }
   if (s.p == 3) return launch_leaf<T, 3, 2, 9>(s, a, st);

@@ -51,3 +51,33 @@ def test_pool_score_edges(N, Hq, Hkv, D, p, L, dt):
                     check_equal(f"scores[{b},{hh}]", s[b, hh], oracle.scores(h, rows))
                 if R:
                     check_equal(f"pyramid[{b},{hh}]", to64(py[b, :, hh]), oracle.pool(h, rows)[N:])
+
+
+@pytest.mark.parametrize("B", [44, 45])
+def test_walk_and_leaves_agree(B):
+    """p = 4, L = 6, D = 128, 16 head slots: batches of 45 give the walk 720 workgroups, from which it is
+    launched; one batch alone runs in leaves. Bit for bit alike, and against the oracle."""
+    N, Hq, Hkv, D, p, L = 16384, 12, 2, 128, 4, 6
+    print(f"[pool edges walk] B={B}", flush=True)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(B)
+    x = [torch.randn(B, N, H, D, device=DEV, generator=g).to(torch.bfloat16) for H in (Hq, Hkv, Hkv)]
+
+    def run(B, x):
+        pr = lh.problem(B, N, Hq, Hkv, D, p, L, 1, torch.bfloat16)
+        Ptot = lh.lh_pyramid_rows(pr)
+        nan = float("nan")
+        pyr = [torch.full((B, Ptot - N, H, D), nan, dtype=torch.bfloat16, device=DEV) for H in (Hq, Hkv, Hkv)]
+        s = [torch.full((B, H, Ptot), nan, device=DEV) for H in (Hq, Hkv)]
+        lh.lh_pool_score(pr, *x, *pyr, *s)
+        torch.cuda.synchronize()
+        return pyr + s
+
+    all_ = run(B, x)
+    for b in range(B):
+        for a, one in zip(all_, run(1, [t[b:b + 1] for t in x])):
+            assert torch.equal(a[b:b + 1], one), b
+    h = oracle.Head(N, D, p, L, 1, oracle.BF16)
+    rows = x[0][B - 1, :, Hq - 1].double().cpu().numpy()
+    check_equal("scores", all_[3][B - 1, Hq - 1], oracle.scores(h, rows))
+    check_equal("pyramid", to64(all_[0][B - 1, :, Hq - 1]), oracle.pool(h, rows)[N:])
