@@ -675,10 +675,12 @@ hipError_t lh_launch_select(const LhShape& s, const float* s_qk, const float* s_
     o.cand[l] = (int32_t)s.cand[l];
     o.lsh[l] = pow2 ? l * pl : -1;
   }
-  // Ranges of 8192 window ends share the cost of a range's searches best; where they leave the chip
-  // idle, ranges of 1024. At N = 8192, 8 selections 28 -> 25 us with the selection; 65,536, 8, L = 1
-  // 28 -> 16.6; 524,288, 8 (512 ranges of 8192) 109 and 127 with ranges of 1024.
-  const bool small = (s.N + 8191) / 8192 * BH < 256;
+  // Ranges of 8192 window ends share the cost of a range's searches best; where they leave half the chip
+  // idle (128 or fewer), ranges of 1024. The whole selection with ranges of 1024 and 8192, us: 64 ranges of 8192 (N =
+  // 8192, 64 heads, p = 4, L = 3) 21.9 and 26.0; 128 26.3 and 26.4 (N = 32,768, 32 heads 32.8 and 35.0); 192 33.6 and
+  // 27.6 (32,768, 48 38.8 and 36.0); 256 36.4 and 29.4; 192 at L = 6, p = 2 52.1 and 45.6; L = 1 25.0 and 21.4
+  // (N = 32,768, 48 heads 26.3 and 27.8).
+  const bool small = (s.N + 8191) / 8192 * BH <= 128;
   const int E = small ? 1024 : 8192;
   const dim3 grid((unsigned)((s.N + E - 1) / E), (unsigned)BH);
 #define LH_ORDER_CASE(LL)                                                                              \

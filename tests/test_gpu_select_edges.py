@@ -47,10 +47,10 @@ def test_bin_sizes(N, p, L, k, flags, inbin, ties, rng):
 
 
 @pytest.mark.parametrize("flags", [0, 1])
-@pytest.mark.parametrize("N,p,L,k,H", [(20000, 5, 3, 300, 85), (20000, 5, 3, 300, 86), (9999, 3, 3, 200, 128),
-                                       (19683, 3, 5, 50, 86), (16400, 2, 5, 40, 86)])
+@pytest.mark.parametrize("N,p,L,k,H", [(20000, 5, 3, 300, 42), (20000, 5, 3, 300, 43), (9999, 3, 3, 200, 64),
+                                       (9999, 3, 3, 200, 65), (19683, 3, 5, 50, 43), (16400, 2, 5, 40, 43)])
 def test_order_ranges(N, p, L, k, H, flags, rng):
-    """Selections x ranges of 8192 window ends: 255 (ranges of 1024 run) and 256 or more; with p = 3 and
+    """Selections x ranges of 8192 window ends: 126 and 128 (ranges of 1024 run), 129 and 130; with p = 3 and
     5 a range's edge lies inside windows of every level; at N = 16,400 the last range holds one window."""
     print(f"[select edges order] N={N} p={p} L={L} k={k} H={H} flags={flags}", flush=True)
     N -= N % p ** (L - 1)

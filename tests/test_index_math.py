@@ -82,7 +82,7 @@ def _cases():
 
 CASES = _cases()
 
-# Window ends per workgroup of order_kernel: 8192, and 1024 where those are fewer than 256 workgroups.
+# Window ends per workgroup of order_kernel: 8192, and 1024 where those would be 128 workgroups or fewer.
 ORDER_RANGES = (1024, 8192)
 
 
