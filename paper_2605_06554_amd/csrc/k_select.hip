@@ -321,22 +321,24 @@ __global__ void __launch_bounds__(kSelThreads) select_kernel(SelArgs a) {
           // four lanes per key, each against every fourth 16 bytes. Places past m hold 0, which no key
           // is below; counted with keys of 0, they move no key's place.
           static_assert(4 * kRankKeys <= kSelThreads, "four lanes per key");
-          const uint32_t key = bin_keys[(tid >> 2) & (kRankKeys - 1)];
-          uint32_t above = 0, same = 0;
+          if ((tid >> 2) < m) {
+            const uint32_t key = bin_keys[tid >> 2];
+            uint32_t above = 0, same = 0;
 #pragma unroll 4
-          for (int j = 4 * (tid & 3); j < m; j += 16) {
-            const u32x4 o = *reinterpret_cast<const u32x4*>(bin_keys + j);
-            above += (o.x > key) + (o.y > key) + (o.z > key) + (o.w > key);
-            same += (o.x == key) + (o.y == key) + (o.z == key) + (o.w == key);
-          }
+            for (int j = 4 * (tid & 3); j < m; j += 16) {
+              const u32x4 o = *reinterpret_cast<const u32x4*>(bin_keys + j);
+              above += (o.x > key) + (o.y > key) + (o.z > key) + (o.w > key);
+              same += (o.x == key) + (o.y == key) + (o.z == key) + (o.w == key);
+            }
 #pragma unroll
-          for (int d = 1; d <= 2; d <<= 1) {
-            above += __shfl_xor(above, d, 64);
-            same += __shfl_xor(same, d, 64);
-          }
-          if ((tid >> 2) < m && above < rem && above + same >= rem) {  // every equal key writes the same
-            sel_state[0] = key;
-            sel_state[1] = rem - above;
+            for (int d = 1; d <= 2; d <<= 1) {
+              above += __shfl_xor(above, d, 64);
+              same += __shfl_xor(same, d, 64);
+            }
+            if (above < rem && above + same >= rem) {  // every equal key writes the same
+              sel_state[0] = key;
+              sel_state[1] = rem - above;
+            }
           }
           __syncthreads();
           break;
