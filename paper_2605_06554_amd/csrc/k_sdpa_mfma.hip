@@ -35,6 +35,8 @@
 // until its own LDS-DMA loads have landed, then the block barrier publishes tile t from every
 // wave; right after the barrier the loads of tile t + 1 go into the slot tile t - 1 used. Loads
 // past the end read clamped rows into the free slot.
+#include <math.h>
+
 #include <type_traits>
 
 #include "lh_common.h"
@@ -1070,33 +1072,78 @@ sdpa_bwd_bf16(BwdArgs a, SdpaIdx ix, HeadMap hm) {
                         a.scale, ix, hm);
 }
 
-// The split F of a launch (FwdCfg, BwdCfg) by the number of 32-row blocks of all heads, from
-// sweeps of S = 2000 .. 24,000 rows and 1 .. 28 heads at D = 64 and 128, every F timed in turn.
-// Forward, us for F = 1, 2, 4 (the lines are the same at both D). F = 4 to 2, D = 128: 1099 blocks (5000
-// rows, 7 heads) 172, 84.5, 82.2; 1125 (12,000, 3) 400, 194, 174; 1222 (3000, 13) 105, 54.7, 65.5; 1256
-// (5000, 8) 171, 83.9, 85.4; D = 64: 1128 (3000, 12) 72.8, 36.7, 35.5; 1222 76.1, 37.6, 39.3; 1256 118,
-// 58.6, 56.6. F = 2 to 1, D = 128: 3375 (12,000, 9) 448, 402, 515; 3760 (6000, 20) 226, 219, 278; 4125 (12,000, 11)
-// 473, 482, 628; 4500 472, 499, 608; D = 64: 3760 150, 145, 172; 4136 (6000, 22) 153, 162, 193.
-static int fwd_split(const LhShape& s) {
-  const int64_t nb = (s.S + 31) / 32 * s.B * s.Hq;
-  return nb <= 1150 ? 4 : nb <= 3950 ? 2 : 1;
+// The split F of a launch (FwdCfg, BwdCfg): the one whose workgroups, taken in launch order by 256 CUs, one
+// at a time, end first. A workgroup takes `fixed` us and `tile` us per tile; a launch of more than 256
+// takes the longer of its longest chain and an even share of the sum, and somewhat more where both are
+// alike (the 4-norm of the two). The constants are fits to 1200 shapes of each direction (S = 33 ..
+// 24,000, 1 .. 256 heads, groups of 1 .. 8), each timed with every F. Over those the split chosen
+// so takes 0.3% (forward) and 0.4% (backward) longer than the best one, at worst 18%, and over 165 other
+// shapes 0.2% and 0.1%. A line drawn at a number of row blocks took 6 and 7% longer, because rows of up to 1500
+// of many heads fill the chip with any F. Forward, us for F = 1, 2, 4, D = 128: S = 160, 192 heads (one
+// round of 192 workgroups; two; three) 12.7, 16.7, 21.3; 192, 128 12.7, 10.1, 14.8; 512, 64 22.3, 15.8, 18.6;
+// 1438, 64 60.2, 63.7, 82.8; 5000, 7 172, 84.5, 82.2; 24,000, 5 915, 839, 1049; 12,000, 12 472, 499, 608.
+// Backward: S = 160, 96 heads 18.6, 23.2, 31.9; 1024, 48 68.0, 79.4, 108; 2000, 8 95.2, 62.9, 54.7; 8000, 6
+// 392, 344, 420; 10,752, 8 on 2 selections 1975, 1130, 950.
+struct SplitCost {
+  double fixed, tile;
+};
+constexpr SplitCost kFwdCost[2][3] = {{{3.87, 1.43}, {5.33, 0.628}, {4.57, 0.741}},  // D = 64: F = 1, 2, 4
+                                      {{4.90, 2.236}, {6.40, 0.99}, {6.09, 1.20}}};  // D = 128
+constexpr SplitCost kBwdCost[2][3] = {{{2.24, 1.699}, {4.20, 0.948}, {3.57, 1.117}},
+                                      {{3.53, 2.841}, {7.36, 1.613}, {5.61, 2.177}}};
+constexpr int64_t kCUs = 256;
+
+// `jobs` workgroups of `sum` tiles together; tiles(i): of job i in launch order; longest: of the longest job;
+// shortest(i): the fewest tiles among the jobs before job i (forward: and i).
+template <typename Tiles, typename Shortest>
+static double split_time(SplitCost c, int64_t jobs, double sum, int64_t longest, Tiles tiles, Shortest shortest) {
+  double chain = c.fixed + c.tile * longest;
+  if (jobs <= kCUs) return chain;
+  for (int64_t k = 1; k <= 3 && k * kCUs < jobs; ++k) {  // job 256 k comes after k jobs or more of its CU
+    const double x = (k + 1) * c.fixed + c.tile * (k * shortest(k * kCUs) + tiles(k * kCUs));
+    chain = x > chain ? x : chain;
+  }
+  const double share = (c.fixed * jobs + c.tile * sum) / kCUs;
+  return sqrt(sqrt(chain * chain * chain * chain + share * share * share * share));
 }
-// Backward (dK/dV and dQ together), us for F = 1, 2, 4. F = 4 to 2, D = 128: 504 blocks (2000 rows, 8 heads)
-// 95.2, 62.9, 54.7; 567 96.6, 65.5, 66.8; 630 96.2, 65.1, 70.1; at D = 64 the line lies further out: 567 61.1,
-// 40.9, 37.0; 625 (4000, 5) 113, 70.3, 60.8; 693 61.9, 41.5, 43.0; 756 61.0, 40.5, 45.0. F = 2 to 1, D = 128:
-// 1500 (8000, 6) 392, 344, 420; 1598 (3000, 17) 159, 161, 225; 1625 (4000, 13) 209, 208, 279; 1692 160, 167,
-// 221; D = 64: 1500 233, 198, 220; 1625 125, 121, 143; 1692 95.3, 98.2, 118.
-// With a shared selection a dK/dV block is Gq times as long, so the lines lie further out. 4 query
-// heads each, D = 128: 672 blocks (10,752 rows, 2 selections) 1975, 1130, 950; 750 (4000, 6) 752, 446, 465;
-// 1680 (10,752, 5) 2274, 2077, 2528; 2000 (4000, 16) 892, 971, 1166; 2016 (10,752, 6) 2345, 2438, 2907; D =
-// 64: 750 468, 263, 241; 1000 (4000, 8) 470, 290, 312; 2000 505, 517, 596; 2016 1395, 1329, 1533; 2352
-// (10,752, 7) 1492, 1570, 1820.
-static int bwd_split(const LhShape& s) {
-  const int64_t nb = (s.S + 31) / 32 * s.B * s.Hs;
-  const bool d64 = s.D == 64;
-  if (s.Gq > 1) return nb <= (d64 ? 800 : 710) ? 4 : nb <= (d64 ? 2100 : 1850) ? 2 : 1;
-  return nb <= (d64 ? 640 : 560) ? 4 : nb <= 1640 ? 2 : 1;
+
+// The tiles of a head's n row blocks of R rows, tiles of T columns: block j ends at tile ends(j); sum over j.
+struct RowTiles {
+  int64_t S, n;
+  int R, T;
+  RowTiles(int64_t S_, int R_, int T_) : S(S_), n((S_ + R_ - 1) / R_), R(R_), T(T_) {}
+  int64_t ends(int64_t j) const { return ((j + 1 < n ? (j + 1) * R : S) + T - 1) / T; }
+  int64_t starts(int64_t j) const { return j * R / T; }
+  double sum_ends() const { return ends(n - 1) + (R >= T ? (double)(R / T) * n * (n - 1) / 2 : (double)n * n / 4); }
+  double sum_starts() const { return R >= T ? (double)(R / T) * n * (n - 1) / 2 : (double)(n - 1) * (n - 1) / 4; }
+};
+
+template <int F>
+static double fwd_time(const LhShape& s) {
+  const RowTiles t(s.S, FwdCfg<F>::ROWS, FwdCfg<F>::TILE);
+  const int64_t heads = s.B * s.Hq;
+  auto tiles = [&](int64_t i) { return t.ends(t.n - 1 - i / heads); };  // longest first
+  return split_time(kFwdCost[s.D == 128][F / 2], t.n * heads, heads * t.sum_ends(), tiles(0), tiles, tiles);
 }
+
+template <int F>
+static double bwd_time(const LhShape& s) {
+  const RowTiles t(s.S, BwdCfg<F>::ROWS, BwdCfg<F>::TILE);
+  const int64_t kheads = s.B * s.Hs, qheads = s.B * s.Hq, nk = t.n * kheads, all = t.ends(t.n - 1);
+  auto tiles = [&](int64_t i) {  // dK/dV blocks, then dQ blocks, the longest of each first
+    return i < nk ? s.Gq * (all - t.starts(i / kheads)) : t.ends(t.n - 1 - (i - nk) / qheads);
+  };
+  auto shortest = [&](int64_t i) {
+    const int64_t x = tiles(i - 1), y = i <= nk ? x : tiles(nk - 1);
+    return x < y ? x : y;
+  };
+  const double sum = kheads * s.Gq * (t.n * (double)all - t.sum_starts()) + qheads * t.sum_ends();
+  return split_time(kBwdCost[s.D == 128][F / 2], nk + t.n * qheads, sum, s.Gq * all, tiles, shortest);
+}
+
+static int least(double t1, double t2, double t4) { return t4 <= t2 && t4 <= t1 ? 4 : t2 <= t1 ? 2 : 1; }
+static int fwd_split(const LhShape& s) { return least(fwd_time<1>(s), fwd_time<2>(s), fwd_time<4>(s)); }
+static int bwd_split(const LhShape& s) { return least(bwd_time<1>(s), bwd_time<2>(s), bwd_time<4>(s)); }
 
 template <int D, bool IDX, int F>
 static void launch_fwd_F(const LhShape& s, const void* qs, const void* ks, const void* vs, void* os, float* lse,

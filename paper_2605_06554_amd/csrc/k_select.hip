@@ -16,9 +16,11 @@
 // No floating-point atomics: the result is bitwise deterministic.
 // Bound: latency of one workgroup's chain, two barriers or more a step. Ranking the first digit's bin
 // instead of two more digits, loads in batches that fit the level, and the order kernel's shorter
-// ranges took the two kernels at N = 8192, 8 heads, L = 3 from 31 to 22 us; 16,384, 16 heads, L = 4 35
-// -> 24; 2048, 2 heads, L = 6 35 -> 27; with the keys in global memory (524,288, 8 heads, k = 16,384)
-// 8 reads in flight took 192 to 161.
+// ranges took the two kernels at N = 8192, 8 heads, L = 3 from 29 to 20 us; 16,384, 16 heads, L = 4 33
+// -> 22; 2048, 2 heads, L = 6 45 -> 33; with the keys in global memory (524,288, 8 heads, k = 16,384) 192
+// -> 145, with 8 reads in flight. Four lanes rank a key: one lane a key made levels of 10,000 and more
+// candidates slower than the digits (41.9 us with digits, 48.0 with one lane, 38.1 now: 27,505 candidates, 24
+// selections).
 //
 // order_kernel: emitted entries are sorted by key = e * L + (L - 1 - l), e = (i + 1) p^l - 1
 // (window end, coarser level first on ties). A workgroup owns a range of window ends: its
