@@ -16,11 +16,11 @@
 // No floating-point atomics: the result is bitwise deterministic.
 // Bound: latency of one workgroup's chain, two barriers or more a step. Ranking the first digit's bin
 // instead of two more digits, loads in batches that fit the level, and the order kernel's shorter
-// ranges took the two kernels at N = 8192, 8 heads, L = 3 from 29 to 20 us; 16,384, 16 heads, L = 4 33
-// -> 22; 2048, 2 heads, L = 6 45 -> 33; with the keys in global memory (524,288, 8 heads, k = 16,384) 192
-// -> 145, with 8 reads in flight. Four lanes rank a key: one lane a key made levels of 10,000 and more
-// candidates slower than the digits (41.9 us with digits, 48.0 with one lane, 38.1 now: 27,505 candidates, 24
-// selections).
+// ranges took the two kernels at N = 8192, 8 heads, L = 3 from 29 to 19 us; 16,384, 16 heads, L = 4 33
+// -> 21; 2048, 2 heads, L = 6 48 -> 33; with the keys in global memory (524,288, 8 heads, k = 16,384) 191
+// -> 149, with 8 reads in flight. The ranking reads 16 bytes at a time, 64 in flight: one key at a time, levels
+// of 10,000 and more candidates were slower than with the digits (110,020 rows, 24 heads, p = 2, L = 2, two
+// batches 59.3 us with digits, 62.6, now 55.6). Four lanes a key gain 1 to 3% there and lose 2% on short levels.
 //
 // order_kernel: emitted entries are sorted by key = e * L + (L - 1 - l), e = (i + 1) p^l - 1
 // (window end, coarser level first on ties). A workgroup owns a range of window ends: its
@@ -320,22 +320,16 @@ __global__ void __launch_bounds__(kSelThreads) select_kernel(SelArgs a) {
             }
           });
           __syncthreads();
-          // four lanes per key, each against every fourth 16 bytes. Places past m hold 0, which no key
-          // is below; counted with keys of 0, they move no key's place.
-          static_assert(4 * kRankKeys <= kSelThreads, "four lanes per key");
-          if ((tid >> 2) < m) {
-            const uint32_t key = bin_keys[tid >> 2];
+          // one lane per key, against 4 keys a read. Places past m hold 0, which no key is below;
+          // counted with keys of 0, they move no key's place.
+          if (tid < m) {
+            const uint32_t key = bin_keys[tid];
             uint32_t above = 0, same = 0;
 #pragma unroll 4
-            for (int j = 4 * (tid & 3); j < m; j += 16) {
+            for (int j = 0; j < m; j += 4) {
               const u32x4 o = *reinterpret_cast<const u32x4*>(bin_keys + j);
               above += (o.x > key) + (o.y > key) + (o.z > key) + (o.w > key);
               same += (o.x == key) + (o.y == key) + (o.z == key) + (o.w == key);
-            }
-#pragma unroll
-            for (int d = 1; d <= 2; d <<= 1) {
-              above += __shfl_xor(above, d, 64);
-              same += __shfl_xor(same, d, 64);
             }
             if (above < rem && above + same >= rem) {  // every equal key writes the same
               sel_state[0] = key;
