@@ -368,12 +368,13 @@ sdpa_fwd_f32(const float* __restrict__ Q, const float* __restrict__ K, const flo
   float* kt = Kt[f];
   float* vt = Vt[f];
   const T tl(lane);
-  Split8 q[D / 16];
-  load_row_regs<D>(Q + bh * S * D, myq < S ? myq : S - 1, h, q);
   f32x16 o[D / 32];
   float m, l;
   const int nt = qb + 1;  // key tiles 0 .. qb; only the last is masked
   auto pass = [&](auto again) __attribute__((always_inline)) {
+    // (of a pass: its registers, kept for a second one, would be copied aside first: 1 us at D = 128)
+    Split8 q[D / 16];
+    load_row_regs<D>(Q + bh * S * D, myq < S ? myq : S - 1, h, q);
 #pragma unroll
     for (int d = 0; d < D / 32; ++d) o[d] = f32x16{};
     // the running maximum of the unscaled logits starts at the lowest finite value: a masked logit
@@ -427,7 +428,7 @@ sdpa_fwd_f32(const float* __restrict__ Q, const float* __restrict__ K, const flo
   pass(std::false_type{});
   // the wave of the masked tile forms its sums once more, with that tile contained, where they hold
   // what is not finite
-  if (f == (nt - 1) % NF && !sums_finite<D>(o)) pass(std::true_type{});
+  if (__builtin_expect(f == (nt - 1) % NF && !sums_finite<D>(o), 0)) pass(std::true_type{});
   l += __shfl_xor(l, 32, 64);
   put_acc<D>(kt, o, lane);
   if (h == 0) ms[f][r32] = m, ls[f][r32] = l;
