@@ -1074,11 +1074,11 @@ sdpa_bwd_bf16(BwdArgs a, SdpaIdx ix, HeadMap hm) {
 
 // The split F of a launch (FwdCfg, BwdCfg): the one whose workgroups, taken in launch order by 256 CUs, one
 // at a time, end first. A workgroup takes `fixed` us and `tile` us per tile; a launch of more than 256
-// takes the longer of its longest chain and an even share of the sum, and somewhat more where both are
-// alike (the 4-norm of the two). The constants are fits to 1200 shapes of each direction (S = 33 ..
-// 24,000, 1 .. 256 heads, groups of 1 .. 8), each timed with every F. Over those the split chosen
-// so takes 0.3% (forward) and 0.4% (backward) longer than the best one, at worst 18%, and over 165 other
-// shapes 0.2% and 0.1%. A line drawn at a number of row blocks took 6 and 7% longer, because rows of up to 1500
+// takes the longer of its longest chain and an even share of the sum, and with more than two a CU somewhat
+// more where both are alike (the 4-norm of the two). The constants are fits to 3800 shapes of each direction
+// (S = 33 .. 130,000, 1 .. 256 heads, groups of 1 .. 8), each timed with every F. Over those the split chosen
+// so takes 0.1% (forward) and 0.2% (backward) longer than the best one, at worst 18%; on shapes that the fit
+// did not see 0.1 and 0.2% too. Lines drawn at numbers of row blocks took 1% longer, and on rows of up to 1500 7%: those
 // of many heads fill the chip with any F. Forward, us for F = 1, 2, 4, D = 128: S = 160, 192 heads (one
 // round of 192 workgroups; two; three) 12.7, 16.7, 21.3; 192, 128 12.7, 10.1, 14.8; 512, 64 22.3, 15.8, 18.6;
 // 1438, 64 60.2, 63.7, 82.8; 5000, 7 172, 84.5, 82.2; 24,000, 5 915, 839, 1049; 12,000, 12 472, 499, 608.
@@ -1087,10 +1087,10 @@ sdpa_bwd_bf16(BwdArgs a, SdpaIdx ix, HeadMap hm) {
 struct SplitCost {
   double fixed, tile;
 };
-constexpr SplitCost kFwdCost[2][3] = {{{3.87, 1.43}, {5.33, 0.628}, {4.57, 0.741}},  // D = 64: F = 1, 2, 4
-                                      {{4.90, 2.236}, {6.40, 0.99}, {6.09, 1.20}}};  // D = 128
-constexpr SplitCost kBwdCost[2][3] = {{{2.24, 1.699}, {4.20, 0.948}, {3.57, 1.117}},
-                                      {{3.53, 2.841}, {7.36, 1.613}, {5.61, 2.177}}};
+constexpr SplitCost kFwdCost[2][3] = {{{3.72, 1.479}, {4.84, 0.604}, {4.55, 0.664}},   // D = 64: F = 1, 2, 4
+                                      {{4.60, 2.20}, {6.52, 0.949}, {6.74, 1.21}}};  // D = 128
+constexpr SplitCost kBwdCost[2][3] = {{{1.63, 1.772}, {3.96, 0.96}, {3.61, 1.092}},
+                                      {{2.42, 2.954}, {6.49, 1.671}, {6.27, 2.107}}};
 constexpr int64_t kCUs = 256;
 
 // `jobs` workgroups of `sum` tiles together; tiles(i): of job i in launch order; longest: of the longest job;
@@ -1104,6 +1104,7 @@ static double split_time(SplitCost c, int64_t jobs, double sum, int64_t longest,
     chain = x > chain ? x : chain;
   }
   const double share = (c.fixed * jobs + c.tile * sum) / kCUs;
+  if (jobs <= 2 * kCUs) return share > chain ? share : chain;
   return sqrt(sqrt(chain * chain * chain * chain + share * share * share * share));
 }
 
