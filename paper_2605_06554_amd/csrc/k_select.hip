@@ -19,8 +19,8 @@
 // ranges took the two kernels at N = 8192, 8 heads, L = 3 from 29 to 19 us; 16,384, 16 heads, L = 4 33
 // -> 21; 2048, 2 heads, L = 6 48 -> 33; with the keys in global memory (524,288, 8 heads, k = 16,384) 191
 // -> 149, with 8 reads in flight. The ranking reads 16 bytes at a time, 64 in flight: one key at a time, levels
-// of 10,000 and more candidates were slower than with the digits (110,020 rows, 24 heads, p = 2, L = 2, two
-// batches 59.3 us with digits, 62.6, now 55.6). Four lanes a key gain 1 to 3% there and lose 2% on short levels.
+// of 10,000 and more candidates were slower than with the digits (two batches of 55,010
+// rows, 12 / 3 heads, p = 2, L = 2, k = 6180 59 us with digits, 63, now 56). Four lanes a key gain 1 to 3% there and lose 2% on short levels.
 //
 // order_kernel: emitted entries are sorted by key = e * L + (L - 1 - l), e = (i + 1) p^l - 1
 // (window end, coarser level first on ties). A workgroup owns a range of window ends: its
